@@ -434,26 +434,6 @@ __global__ __launch_bounds__(256) void k_deposit_adjoint(KParams kp, AdjIn in, i
   }
 }
 
-// rhs of the transposed solve: l_th + l_E1/theta - c dt C_CN l_B1  (curl precomputed in t)
-__global__ __launch_bounds__(256) void k_adj_rhs(size_t n3, double theta, double cdt, const double *__restrict__ lth,
-                                                 const double *__restrict__ lE1, const double *__restrict__ ccn_lB1,
-                                                 double *__restrict__ out) {
-  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= n3) return;
-  out[i] = lth[i] + lE1[i] / theta - cdt * ccn_lB1[i];
-}
-
-// l_En = -(1-theta)/theta l_E1 + mu ;  l_Bn += l_B1 + c theta dt C_NC mu (curl precomputed)
-__global__ __launch_bounds__(256) void k_adj_finish(size_t n3, double theta, double ctdt, const double *__restrict__ lE1,
-                                                    const double *__restrict__ lB1, const double *__restrict__ mu,
-                                                    const double *__restrict__ cnc_mu, double *__restrict__ lEn,
-                                                    double *__restrict__ lBn) {
-  const size_t i = (size_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= n3) return;
-  lEn[i] += -(1.0 - theta) / theta * lE1[i] + mu[i];
-  lBn[i] += lB1[i] + ctdt * cnc_mu[i];
-}
-
 }  // namespace
 
 void launch_push_adjoint(const KParams &kp, const AdjInPtrs &in, int n, const double *Eth, const double *B,
@@ -479,17 +459,6 @@ void launch_deposit_adjoint(const KParams &kp, const AdjInPtrs &in, int n, const
     hipLaunchKernelGGL(k_deposit_adjoint<2>, dim3(nb), dim3(256), 0, st, kp, a, n, B, Eth, mu, lx_out, lu_out, lB);
   else
     hipLaunchKernelGGL(k_deposit_adjoint<3>, dim3(nb), dim3(256), 0, st, kp, a, n, B, Eth, mu, lx_out, lu_out, lB);
-}
-
-void launch_adj_rhs(size_t n3, double theta, double cdt, const double *lth, const double *lE1, const double *ccn_lB1,
-                    double *out, hipStream_t st) {
-  hipLaunchKernelGGL(k_adj_rhs, dim3((n3 + 255) / 256), dim3(256), 0, st, n3, theta, cdt, lth, lE1, ccn_lB1, out);
-}
-
-void launch_adj_finish(size_t n3, double theta, double ctdt, const double *lE1, const double *lB1, const double *mu,
-                       const double *cnc_mu, double *lEn, double *lBn, hipStream_t st) {
-  hipLaunchKernelGGL(k_adj_finish, dim3((n3 + 255) / 256), dim3(256), 0, st, n3, theta, ctdt, lE1, lB1, mu, cnc_mu, lEn,
-                     lBn);
 }
 
 }  // namespace relsim

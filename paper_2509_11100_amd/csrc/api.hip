@@ -43,6 +43,9 @@ struct relsim_ctx {
   // its second pass), or 0 when no such push has happened since the last
   // call that could change the particle state
   int push_ke_parts = 0;
+  // Arnoldi steps the last solve took (from E^n, from a guess, transposed):
+  // how many the next one enqueues before it looks
+  int expect[3] = {9, 9, 9};
   // timing
   bool timing = false;
   std::vector<hipEvent_t> pool;
@@ -150,6 +153,9 @@ int validate(const relsim_params *p, std::string &msg) {
   return RELSIM_OK;
 }
 
+// Stride of the Krylov basis's rows: even, for 16-byte access.
+size_t gm_stride(size_t n3) { return (n3 + 1) & ~(size_t)1; }
+
 Layout make_layout(const relsim_params *p) {
   Layout L{};
   const size_t nc = (size_t)p->nx * p->ny * (p->dim == 3 ? p->nz : 1);
@@ -171,12 +177,13 @@ Layout make_layout(const relsim_params *p) {
   L.scan_tmp = take(std::max(scan_tmp_elems((int)nb + 1), scan_tmp_elems((int)gsort_tmp_elems(np))) * 4 + 64);
   L.dirc = take(np);
   L.err = take(64);
-  L.gm_V = take((size_t)(p->gmres_restart + 1) * n3 * 8);
+  L.gm_V = take((size_t)(p->gmres_restart + 1) * gm_stride(n3) * 8);
   L.gm_t = take(n3 * 8);
   L.gm_b = take(n3 * 8);
-  L.gm_r = take(n3 * 8);
-  L.gm_part = take((size_t)kDotBlocks * (kMaxRestart + 2) * 8);
-  L.gm_small = take(4 * (kMaxRestart + 2) * 8);
+  L.gm_r = take(gm_stride(n3) * 8);
+  L.gm_part = take(((size_t)kGmNodeBlocks * (2 * kMaxRestart + 3) + kGmVecBlocks) * 8);
+  L.gm_state = take(sizeof(GmState));
+  L.red_res = take(8 * 8);
   L.red_part = take((size_t)kRedBlocks * 8 * 4);
   L.gs_k0 = take(np * 4);
   L.gs_k1 = take(np * 4);
@@ -419,31 +426,12 @@ int fetch(relsim_ctx *c, const double *dev, int k) {
   return RELSIM_OK;
 }
 
-// out = A x   (uses gm_t as the curl scratch)
-void apply_A(relsim_ctx *c, const void *M, const double *x, double *out) {
+// out = A x or A^T x (gm_t is the 3D curl's scratch)
+void apply_A(relsim_ctx *c, bool transpose, const void *M, const double *x, double *out) {
   double *t = c->at<double>(c->L.gm_t);
-  timed(c, "curl_nc", [&] { launch_curl(c->kp, x, t, 1, c->st); });
-  timed(c, "apply_A", [&] { launch_apply_A_tail(c->kp, c->p.mass_fp32, M, x, t, out, c->st); });
-}
-
-// out = A^T x
-void apply_AT(relsim_ctx *c, const void *M, const double *x, double *out) {
-  double *t = c->at<double>(c->L.gm_t);
-  timed(c, "curl_nc", [&] { launch_curl(c->kp, x, t, 1, c->st); });
-  timed(c, "apply_AT", [&] { launch_apply_AT_tail(c->kp, c->p.mass_fp32, M, x, t, out, c->st); });
-}
-
-int norm2(relsim_ctx *c, const double *x, size_t n, double *out) {
-  double *part = c->at<double>(c->L.red_part);
-  double *res = c->at<double>(c->L.gm_small) + 3 * (kMaxRestart + 2);
-  timed(c, "sumsq", [&] {
-    launch_sumsq_partials(x, n, part, c->st);
-    launch_reduce_partials(part, kRedBlocks, 1, res, c->st);
-  });
-  int rc = fetch(c, res, 1);
-  if (rc) return rc;
-  *out = std::sqrt(c->host[0]);
-  return RELSIM_OK;
+  if (c->kp.dim == 3) timed(c, "curl_nc", [&] { launch_curl(c->kp, x, t, 1, c->st); });
+  timed(c, transpose ? "apply_AT" : "apply_A",
+        [&] { launch_apply(c->kp, c->p.mass_fp32, transpose, M, x, t, out, c->st); });
 }
 
 }  // namespace
@@ -693,7 +681,7 @@ int relsim_energy(relsim_ctx *c, const relsim_particles *pt, const double *E, co
   if (rc) return rc;
   const int G = choose_group(c, pt->n);
   double *part = c->at<double>(c->L.red_part);
-  double *res = c->at<double>(c->L.gm_small);
+  double *res = c->at<double>(c->L.red_res);
   timed(c, "kinetic", [&] {
     enqueue_kinetic(c->kp, c->p.precision, G, front(pt), c->at<double>(c->L.kin_part), part, res, c->st);
   });
@@ -716,7 +704,7 @@ int relsim_energy_pushed(relsim_ctx *c, const double *E, const double *B, double
   int rc = check_flags(c);
   if (rc) return rc;
   double *part = c->at<double>(c->L.red_part);
-  double *res = c->at<double>(c->L.gm_small);
+  double *res = c->at<double>(c->L.red_res);
   timed(c, "kinetic_reduce", [&] {
     launch_reduce_long(c->at<double>(c->L.push_ke), c->push_ke_parts, part, res, c->st);
   });
@@ -746,132 +734,85 @@ int relsim_curl_cn(relsim_ctx *c, const double *in, double *out) {
 int relsim_apply_A(relsim_ctx *c, const void *M, const double *x, double *out) {
   if (!c || !M || !x || !out) return RELSIM_EINVAL;
   if (x == out) return fail(c, RELSIM_EINVAL, "relsim_apply_A cannot work in place");
-  apply_A(c, M, x, out);
+  apply_A(c, false, M, x, out);
   return launch_status(c, "relsim_apply_A");
 }
 
 }  // extern "C"
 
-// Restarted GMRES for A x = b (or A^T x = b) from the initial guess in x.
-// b must live in the workspace slot gm_b.  Returns RELSIM_OK, or
-// RELSIM_ENOTCONVERGED with the last iterate in x.
-static int gmres_solve(relsim_ctx *c, const void *M, bool transpose, double *x, int32_t *iters, double *rel_resid) {
-  const size_t n3 = 3 * (size_t)c->kp.ncells;
-  const int m = c->p.gmres_restart;
-  double *V = c->at<double>(c->L.gm_V);
-  double *b = c->at<double>(c->L.gm_b);
-  double *r = c->at<double>(c->L.gm_r);
-  double *part = c->at<double>(c->L.gm_part);
-  double *hdev = c->at<double>(c->L.gm_small);
-  double *ydev = hdev + (kMaxRestart + 2);
-  double *h1dev = hdev, *h2dev = hdev + 2 * (kMaxRestart + 2);
-  auto op = [&](const double *in, double *out) {
-    if (transpose)
-      apply_AT(c, M, in, out);
-    else
-      apply_A(c, M, in, out);
-  };
-  int rc;
-  double bnorm;
-  rc = norm2(c, b, n3, &bnorm);
-  if (rc) return rc;
-  if (!std::isfinite(bnorm)) return fail(c, RELSIM_ENONFINITE, "right-hand side is not finite");
-  const double tol = c->p.gmres_rtol * bnorm;
-  int total_it = 0;
-  double rel = 0.0;
-  bool converged = false;
-  std::vector<double> H((size_t)(m + 1) * m), cs(m), sn(m), g(m + 1), y(m);
+// Restarted GMRES for A x = b or A^T x = b.  `start` enqueues the kernels that
+// form b, the initial guess in x and its residual, `finish` those that test
+// the final residual and write the caller's outputs.  The device runs the
+// iteration (gmres.hip); the host enqueues as many Arnoldi steps as the last
+// solve of this kind (`expect`) took plus one (surplus steps return at once,
+// about 2.6 us per kernel; a step too few costs a 16 us round trip), the
+// update, the true residual and the finish, and waits once.  Returns
+// RELSIM_OK, RELSIM_ENOTCONVERGED with the last iterate in x, or an error.
+template <typename Start, typename Finish>
+static int gmres_solve(relsim_ctx *c, const void *M, bool transpose, double *x, int &expect, Start &&start,
+                       Finish &&finish, int32_t *iters, double *rel_resid) {
+  GmBuf gm;
+  gm.n3 = 3 * (size_t)c->kp.ncells;
+  gm.ld = gm_stride(gm.n3);
+  gm.V = c->at<double>(c->L.gm_V);
+  gm.t = c->at<double>(c->L.gm_t);
+  gm.b = c->at<double>(c->L.gm_b);
+  gm.r = c->at<double>(c->L.gm_r);
+  gm.p1 = c->at<double>(c->L.gm_part);
+  gm.p3 = gm.p1 + (size_t)kGmNodeBlocks * (2 * kMaxRestart + 1);
+  gm.p2 = gm.p3 + 2 * kGmNodeBlocks;
+  gm.st = c->at<GmState>(c->L.gm_state);
+  gm.m = c->p.gmres_restart;
+  gm.maxit = c->p.gmres_maxit;
+  gm.rtol = c->p.gmres_rtol;
+  gm_blocks(c->kp, gm);
+  timed(c, "gmres_start", [&] { start(gm); });
+  GmHead h{};
+  int j = 0, cycle = 0;  // columns whose operator is enqueued, and their cycle
+  int more = 2;          // columns to enqueue past the expected ones
   for (;;) {
-    // true residual r = b - A x
-    op(x, r);
-    timed(c, "axpby", [&] { launch_axpby(1.0, b, -1.0, r, n3, c->st); });
-    double beta;
-    rc = norm2(c, r, n3, &beta);
+    int batch = expect + 1 - h.total_it;
+    if (batch <= 0) batch = more = std::min(2 * more, kMaxRestart);
+    const int jend = std::min(j + batch, gm.m);
+    auto apply = [&] {
+      timed(c, "gmres_apply", [&] { launch_gm_apply(c->kp, gm, c->p.mass_fp32, transpose, M, j, cycle == 0, c->st); });
+    };
+    if (j == 0) apply();
+    while (j < jend) {
+      timed(c, "gmres_ortho", [&] { launch_gm_ortho(gm, j, c->st); });
+      ++j;
+      apply();
+    }
+    timed(c, "gmres_update", [&] { launch_gm_update(gm, x, c->st); });
+    timed(c, "gmres_residual", [&] { launch_gm_residual(c->kp, gm, c->p.mass_fp32, transpose, M, x, c->st); });
+    timed(c, "field_update", [&] { finish(gm); });
+    const int rc = launch_status(c, "field solve");
     if (rc) return rc;
-    if (!std::isfinite(beta)) return fail(c, RELSIM_ENONFINITE, "GMRES residual is not finite");
-    rel = bnorm > 0 ? beta / bnorm : 0.0;
-    if (beta <= tol) {
-      converged = true;
-      break;
-    }
-    if (total_it >= c->p.gmres_maxit) break;
-    timed(c, "axpby", [&] { launch_axpby(1.0 / beta, r, 0.0, V, n3, c->st); });
-    std::fill(H.begin(), H.end(), 0.0);
-    std::fill(g.begin(), g.end(), 0.0);
-    g[0] = beta;
-    int jdone = 0;
-    for (int j = 0; j < m; ++j) {
-      double *vj = V + (size_t)j * n3;
-      double *w = V + (size_t)(j + 1) * n3;
-      op(vj, w);
-      // classical Gram-Schmidt, twice, with the coefficients staying on the
-      // device: h1, then the correction h2, whose entry j + 1 is |w|^2 after
-      // the first pass.  The first pass's update and the second pass's dots
-      // share one read of the basis, and the second update normalises w by
-      // |w| = sqrt(|w|^2 - |h2|^2) (entry j + 2, 0 if that cancelled and w
-      // was left as it is); one copy to the host per Arnoldi step.
-      timed(c, "mdot", [&] { launch_mdot(V, n3, j + 1, w, n3, part, h1dev, c->st); });
-      int fused = 0;
-      timed(c, "maxpy_dot", [&] { fused = launch_maxpy_dot(V, n3, j + 1, h1dev, w, n3, part, h2dev, c->st); });
-      if (!fused) {
-        timed(c, "maxpy", [&] { launch_maxpy(V, n3, j + 1, h1dev, w, n3, c->st); });
-        timed(c, "mdot", [&] { launch_mdot(V, n3, j + 2, w, n3, part, h2dev, c->st); });
-      }
-      timed(c, "maxpy", [&] { launch_maxpy_scale(V, n3, j + 1, h2dev, w, n3, c->st); });
-      rc = fetch(c, hdev, (int)(h2dev - hdev) + j + 3);
-      if (rc) return rc;
-      const double *h1 = c->host, *h2 = c->host + (h2dev - hdev);
-      std::vector<double> h(h1, h1 + j + 1);
-      for (int k = 0; k <= j; ++k) h[k] += h2[k];
-      double hn = h2[j + 2];
-      const bool scaled = hn > 0.0;
-      if (!scaled) {
-        rc = norm2(c, w, n3, &hn);
-        if (rc) return rc;
-      }
-      if (!std::isfinite(hn)) return fail(c, RELSIM_ENONFINITE, "GMRES Arnoldi vector is not finite");
-      for (int k = 0; k <= j; ++k) H[(size_t)k * m + j] = h[k];
-      H[(size_t)(j + 1) * m + j] = hn;
-      for (int k = 0; k < j; ++k) {
-        const double a = H[(size_t)k * m + j], bb = H[(size_t)(k + 1) * m + j];
-        H[(size_t)k * m + j] = cs[k] * a + sn[k] * bb;
-        H[(size_t)(k + 1) * m + j] = -sn[k] * a + cs[k] * bb;
-      }
-      const double a = H[(size_t)j * m + j], bb = H[(size_t)(j + 1) * m + j];
-      const double den = std::hypot(a, bb);
-      cs[j] = den > 0 ? a / den : 1.0;
-      sn[j] = den > 0 ? bb / den : 0.0;
-      H[(size_t)j * m + j] = den;
-      H[(size_t)(j + 1) * m + j] = 0.0;
-      g[j + 1] = -sn[j] * g[j];
-      g[j] = cs[j] * g[j];
-      ++total_it;
-      jdone = j + 1;
-      const bool last = std::fabs(g[j + 1]) <= tol || hn == 0.0 || j == m - 1 || total_it >= c->p.gmres_maxit;
-      if (last) break;
-      if (!scaled) timed(c, "axpby", [&] { launch_axpby(1.0 / hn, w, 0.0, w, n3, c->st); });
-    }
-    // y = H^-1 g (upper triangular), x += V y
-    for (int k = jdone - 1; k >= 0; --k) {
-      double s = g[k];
-      for (int l = k + 1; l < jdone; ++l) s -= H[(size_t)k * m + l] * y[l];
-      y[k] = H[(size_t)k * m + k] != 0.0 ? s / H[(size_t)k * m + k] : 0.0;
-    }
-    for (int k = 0; k < jdone; ++k) c->host[k] = -y[k];
-    HIP_CHECK(c, hipMemcpyAsync(ydev, c->host, sizeof(double) * jdone, hipMemcpyHostToDevice, c->st));
-    timed(c, "maxpy", [&] { launch_maxpy(V, n3, jdone, ydev, x, n3, c->st); });
-    // the copy reads c->host; make sure it finished before the host buffer is reused
+    HIP_CHECK(c, hipMemcpyAsync(c->host, gm.st, sizeof(GmHead), hipMemcpyDeviceToHost, c->st));
     HIP_CHECK(c, hipStreamSynchronize(c->st));
+    std::memcpy(&h, c->host, sizeof(h));
+    switch (h.code) {
+      case 0: break;
+      case kGmRefused: {
+        const int flagged = check_flags(c);
+        return flagged ? flagged : fail(c, RELSIM_EINTERNAL, "error flags changed during the solve");
+      }
+      case kGmBadRhs: return fail(c, RELSIM_ENONFINITE, "right-hand side is not finite");
+      case kGmBadResidual: return fail(c, RELSIM_ENONFINITE, "GMRES residual is not finite");
+      default: return fail(c, RELSIM_ENONFINITE, "GMRES Arnoldi vector is not finite");
+    }
+    if (h.done) break;
+    if (h.cycle != cycle) {
+      cycle = h.cycle;
+      j = 0;
+    }
   }
-  if (iters) *iters = total_it;
-  if (rel_resid) *rel_resid = rel;
-  if (!converged) return fail(c, RELSIM_ENOTCONVERGED, "GMRES reached gmres_maxit before gmres_rtol");
+  expect = h.total_it;
+  if (iters) *iters = h.total_it;
+  if (rel_resid) *rel_resid = h.rel;
+  if (h.done == kGmAtLimit) return fail(c, RELSIM_ENOTCONVERGED, "GMRES reached gmres_maxit before gmres_rtol");
   return RELSIM_OK;
 }
-
-extern "C" {
-
-}  // extern "C"
 
 // S4-S5 from E^n (guess == false) or from E_theta's contents (guess == true).
 static int field_solve(relsim_ctx *c, const void *M, const double *Jhat, const double *E_n, const double *B_n,
@@ -880,18 +821,14 @@ static int field_solve(relsim_ctx *c, const void *M, const double *Jhat, const d
   if (!c) return RELSIM_EINVAL;
   if (!M || !Jhat || !E_n || !B_n || !E_theta || !E_np1 || !B_np1) return fail(c, RELSIM_EINVAL, "null grid array");
   if (E_theta == E_n || E_theta == E_np1 || B_np1 == B_n) return fail(c, RELSIM_EINVAL, "aliased solve arguments");
-  int rc = check_flags(c);
-  if (rc) return rc;
-  const size_t n3 = 3 * (size_t)c->kp.ncells;
-  double *b = c->at<double>(c->L.gm_b);
-  timed(c, "rhs", [&] { launch_rhs(c->kp, E_n, B_n, Jhat, b, c->st); });
-  if (!guess) HIP_CHECK(c, hipMemcpyAsync(E_theta, E_n, n3 * sizeof(double), hipMemcpyDeviceToDevice, c->st));
-  const int solved = gmres_solve(c, M, false, E_theta, iters, rel_resid);
-  if (solved != RELSIM_OK && solved != RELSIM_ENOTCONVERGED) return solved;
-  timed(c, "field_update", [&] { launch_field_update(c->kp, E_n, B_n, E_theta, E_np1, B_np1, c->st); });
-  rc = launch_status(c, guess ? "relsim_field_solve_guess" : "relsim_field_solve");
-  if (rc) return rc;
-  return solved;
+  return gmres_solve(
+      c, M, false, E_theta, c->expect[guess ? 1 : 0],
+      [&](const GmBuf &gm) {
+        launch_gm_start(c->kp, gm, c->p.mass_fp32, M, E_n, B_n, Jhat, guess ? E_theta : E_n, E_theta,
+                        c->at<int32_t>(c->L.err), c->st);
+      },
+      [&](const GmBuf &gm) { launch_gm_finish(c->kp, gm, E_n, B_n, E_theta, E_np1, B_np1, c->st); }, iters,
+      rel_resid);
 }
 
 extern "C" {
@@ -910,7 +847,7 @@ int relsim_field_solve_guess(relsim_ctx *c, const void *M, const double *Jhat, c
 int relsim_apply_AT(relsim_ctx *c, const void *M, const double *x, double *out) {
   if (!c || !M || !x || !out) return RELSIM_EINVAL;
   if (x == out) return fail(c, RELSIM_EINVAL, "relsim_apply_AT cannot work in place");
-  apply_AT(c, M, x, out);
+  apply_A(c, true, M, x, out);
   return launch_status(c, "relsim_apply_AT");
 }
 
@@ -947,26 +884,13 @@ int relsim_field_solve_adjoint(relsim_ctx *c, const void *M, const double *lam_E
   if (!c) return RELSIM_EINVAL;
   if (!M || !lam_E_theta || !lam_E_np1 || !lam_B_np1 || !mu || !lam_E_n || !lam_B_n)
     return fail(c, RELSIM_EINVAL, "null grid array");
-  int rc = check_flags(c);
-  if (rc) return rc;
-  const size_t n3 = 3 * (size_t)c->kp.ncells;
-  const double th = c->kp.theta;
-  double *b = c->at<double>(c->L.gm_b);
-  double *t = c->at<double>(c->L.gm_t);
-  // rhs = l_th + l_E1/theta - c dt C_NC^T l_B1, with C_NC^T = C_CN
-  timed(c, "curl_cn", [&] { launch_curl(c->kp, lam_B_np1, t, 0, c->st); });
-  timed(c, "adj_rhs", [&] { launch_adj_rhs(n3, th, c->kp.c * c->kp.dt, lam_E_theta, lam_E_np1, t, b, c->st); });
-  HIP_CHECK(c, hipMemsetAsync(mu, 0, n3 * sizeof(double), c->st));
-  const int solved = gmres_solve(c, M, true, mu, iters, rel_resid);
-  if (solved != RELSIM_OK && solved != RELSIM_ENOTCONVERGED) return solved;
-  // l_En += -(1-theta)/theta l_E1 + mu ; l_Bn += l_B1 + c theta dt C_CN^T mu, with C_CN^T = C_NC
-  timed(c, "curl_nc", [&] { launch_curl(c->kp, mu, t, 1, c->st); });
-  timed(c, "adj_finish", [&] {
-    launch_adj_finish(n3, th, c->kp.c * th * c->kp.dt, lam_E_np1, lam_B_np1, mu, t, lam_E_n, lam_B_n, c->st);
-  });
-  rc = launch_status(c, "relsim_field_solve_adjoint");
-  if (rc) return rc;
-  return solved;
+  return gmres_solve(
+      c, M, true, mu, c->expect[2],
+      [&](const GmBuf &gm) {
+        launch_gm_adj_start(c->kp, gm, lam_E_theta, lam_E_np1, lam_B_np1, mu, c->at<int32_t>(c->L.err), c->st);
+      },
+      [&](const GmBuf &gm) { launch_gm_adj_finish(c->kp, gm, lam_E_np1, lam_B_np1, mu, lam_E_n, lam_B_n, c->st); },
+      iters, rel_resid);
 }
 
 int relsim_deposit_adjoint(relsim_ctx *c, const relsim_particles *state_n, const double *B_n, const double *E_theta,

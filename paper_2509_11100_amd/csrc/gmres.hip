@@ -1,0 +1,830 @@
+// Restarted GMRES of the implicit field solve (S4-S5 and the transposed
+// solve of the adjoint), FP64.
+//
+// The Krylov iteration runs on the device without the host: the Hessenberg
+// columns, the Givens rotations, the stopping test and the triangular solve
+// are computed by the kernels that need them, and the host enqueues the steps
+// it expects and reads the state once at the end (api.hip).
+//
+// Orthogonalisation: classical Gram-Schmidt twice, with the second pass of a
+// vector delayed until the operator has been applied to it (Bielich, Langou,
+// Thomas, Swirydowicz, Yamazaki and Boman, "Low-synch Gram-Schmidt with
+// delayed reorthogonalization for Krylov solvers", 2022).  Column j starts
+// from w~ = w / |w|, the candidate for v_j after one pass against V =
+// (v_0 .. v_{j-1}):
+//   k_gm_apply  u = A w~, and the sums s = V^T w~, z = V^T u, w~.u
+//   k_gm_ortho  v_j = (w~ - V s) / nu, nu^2 = 1 - |s|^2 (the second pass),
+//               z_j = v_j.u = (w~.u - s.z) / nu, and the next candidate
+//               w = (u - V z - z_j v_j) / nu, with the sum w.w.
+// A V s lies in the span of v_0 .. v_j, so the next candidate needs no other
+// vector; the Hessenberg column is (z - H s) / nu, and the column before gets
+// the second pass's correction s |w|.  Each step reads the basis twice and
+// takes two kernels (three in 3D, where the curl of the vector is formed
+// first), where two plain passes read it three times in three kernels.
+//
+// Each kernel starts by summing the block partial sums that the one before
+// it left: a dependent kernel costs 2.6 us on this device, a separate
+// reduction kernel 4.3 us, and the host round trip that each step used to end
+// with 15 us.  A grid-wide barrier inside one persistent kernel would cost
+// more than a kernel: 3.1 us over 32 blocks, 4.8 over 64, 11.6 over 256.  Sums
+// are taken in a fixed order (per thread, wave, block, then block by block),
+// so a solve is deterministic.
+#include <climits>
+
+#include "field_stencil.h"
+
+namespace relsim {
+namespace {
+
+constexpr int TB = kGmThreads;
+constexpr int NW = TB / 64;
+
+// Block b's groups of TB nodes: group first, first + step, ... below last.
+// Each XCD (blocks are dispatched to the 8 XCDs round robin) works through
+// one contiguous band of the grid, its blocks side by side: a node reads the
+// mass-matrix blocks of the rows below it, which are then in the same L2.
+// gridDim.x is the number of groups, or kGmNodeBlocks (a multiple of 8).
+struct Groups {
+  int first, last, step;
+};
+__device__ __forceinline__ Groups block_groups(int ng) {
+  const int nb = (int)gridDim.x, b = (int)blockIdx.x;
+  if (nb == ng) {
+    const int first = xcd_remap(b, nb);
+    return {first, first + 1, 1};
+  }
+  const int band = (ng + 7) >> 3, x = b & 7;
+  const int lo = x * band;
+  return {lo + (b >> 3), lo + band < ng ? lo + band : ng, nb >> 3};
+}
+
+// Node of thread t in group grp, or -1: in 2D TB consecutive nodes, in 3D
+// TB / 64 chunks of the strip order.
+template <int DIM>
+__device__ __forceinline__ int group_node(const KParams &kp, int grp, int &i, int &j, int &k) {
+  if constexpr (DIM == 2) {
+    const int g = grp * TB + (int)threadIdx.x;
+    j = g / kp.nx;
+    i = g - j * kp.nx;
+    k = 0;
+    return g < kp.ncells ? g : -1;
+  } else {
+    return strip_node(kp.nx, kp.ny, kp.nz, grp * NW + (int)(threadIdx.x >> 6), (int)(threadIdx.x & 63), i, j, k);
+  }
+}
+__host__ __device__ inline int node_groups(const KParams &kp) {
+  return kp.dim == 2 ? (kp.ncells + TB - 1) / TB : grid_node_blocks(kp.nx, kp.ny, kp.nz);
+}
+
+// Sum of acc[q] (q < nv) over the block into P[q * gridDim.x + block].
+template <int NV>
+__device__ __forceinline__ void put_partials(const double (&acc)[NV], int nv, double *lds, double *__restrict__ P) {
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+#pragma unroll
+  for (int q = 0; q < NV; ++q) {
+    if (q < nv) {
+      double v = acc[q];
+#pragma unroll
+      for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
+      if (lane == 0) lds[wid * NV + q] = v;
+    }
+  }
+  __syncthreads();
+  for (int q = threadIdx.x; q < nv; q += TB) {
+    double s = lds[q];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) s += lds[w * NV + q];
+    P[(size_t)q * gridDim.x + blockIdx.x] = s;
+  }
+}
+
+// out[q] (LDS) = the sum over the blocks of partials P[q][.], q < nv; every
+// block forms the same sums.  Ends with a barrier.
+__device__ __forceinline__ void get_sums(const double *__restrict__ P, int nparts, int nv, double *out) {
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  for (int q = wid; q < nv; q += NW) {
+    const double *const p = P + (size_t)q * nparts;
+    double v = 0.0;
+#pragma unroll 4
+    for (int b = lane; b < nparts; b += 64) v += p[b];
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
+    if (lane == 0) out[q] = v;
+  }
+  __syncthreads();
+}
+
+// Whether the kernels of column j have nothing to do: the solve has ended,
+// or its cycle ended with an earlier column.  A block that starts after block
+// 0 of its own kernel has recorded an end would come to the same end.
+__device__ __forceinline__ bool arnoldi_off(const GmState *st, int j) {
+  return st->code != 0 || st->done != 0 || (st->end_at >= 0 && st->end_at < j);
+}
+// The same for the kernels after the Arnoldi steps (update, residual).
+__device__ __forceinline__ bool tail_off(const GmState *st) {
+  return st->code != 0 || st->done != 0 || st->end_at < 0;
+}
+
+// (A x)_g or (A^T x)_g.  In 2D the 3 x 3 nodes around g hold all that the
+// curl of the curl and the mass matrix read, and the curl is formed again for
+// each of the 4 cells around g; in 3D t = C_NC x is given.
+template <int DIM, bool TR, typename MT>
+__device__ __forceinline__ void apply_node(const KParams &kp, const MT *__restrict__ M, const double *__restrict__ x,
+                                           const double *__restrict__ t, int g, int i, int j, int k, double xc[3],
+                                           double out[3]) {
+  const size_t N = (size_t)kp.ncells;
+  const double a = kp.c * kp.theta * kp.dt;
+  const double b = 4.0 * M_PI * kp.theta * kp.dt;
+  double mx[3] = {0.0, 0.0, 0.0}, cc[3];
+  if constexpr (DIM == 2) {
+    int id[9];
+    double x9[3][9];
+    const int im = wrapi(i - 1, kp.nx), ip = wrapi(i + 1, kp.nx);
+    const int jm = kp.nx * wrapi(j - 1, kp.ny), jp = kp.nx * wrapi(j + 1, kp.ny), j0 = kp.nx * j;
+    id[0] = im + jm, id[1] = i + jm, id[2] = ip + jm;
+    id[3] = im + j0, id[4] = g, id[5] = ip + j0;
+    id[6] = im + jp, id[7] = i + jp, id[8] = ip + jp;
+#pragma unroll
+    for (int q = 0; q < 9; ++q)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) x9[c][q] = x[c * N + id[q]];
+#pragma unroll
+    for (int h = 0; h < 5; ++h) {
+#pragma unroll
+      for (int side = 0; side < (h ? 2 : 1); ++side) {
+        // side 0: own block times x at g + delta; side 1: the block of node
+        // g - delta times x there
+        const int q = side ? 4 - h : 4 + h;
+        const MT *Mo = M + (size_t)h * 9 * N + (side ? id[q] : g);
+        double m[9];
+#pragma unroll
+        for (int e = 0; e < 9; ++e) m[e] = (double)Mo[e * N];
+        const double x0 = x9[0][q], x1 = x9[1][q], x2 = x9[2][q];
+        if constexpr (!TR) {
+          mx[0] += m[0] * x0 + m[1] * x1 + m[2] * x2;
+          mx[1] += m[3] * x0 + m[4] * x1 + m[5] * x2;
+          mx[2] += m[6] * x0 + m[7] * x1 + m[8] * x2;
+        } else {
+          mx[0] += m[0] * x0 + m[3] * x1 + m[6] * x2;
+          mx[1] += m[1] * x0 + m[4] * x1 + m[7] * x2;
+          mx[2] += m[2] * x0 + m[5] * x1 + m[8] * x2;
+        }
+      }
+    }
+    double tc[3][8];
+#pragma unroll
+    for (int cell = 0; cell < 4; ++cell) {
+      double c[3][8], r[3];
+#pragma unroll
+      for (int n = 0; n < 4; ++n) {
+        const int q = (cell & 1) + (n & 1) + 3 * ((cell >> 1) + (n >> 1));
+#pragma unroll
+        for (int s = 0; s < 3; ++s) c[s][n] = x9[s][q];
+      }
+      cube_curl<2>(kp, c, r);
+#pragma unroll
+      for (int s = 0; s < 3; ++s) tc[s][cell] = r[s];
+    }
+    cube_curl<2>(kp, tc, cc);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) xc[c] = x9[c][4];
+  } else {
+    double c[3][8];
+    load_cube<3>(kp, t, i - 1, j - 1, k - 1, c);
+    cube_curl<3>(kp, c, cc);
+    apply_M<3, TR, MT>(kp, M, x, g, i, j, k, mx);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) xc[q] = x[q * N + g];
+  }
+#pragma unroll
+  for (int q = 0; q < 3; ++q) out[q] = xc[q] + a * a * cc[q] + b * mx[q];
+}
+
+// out = A x or A^T x (relsim_apply_A, relsim_apply_AT)
+template <int DIM, bool TR, typename MT>
+__global__ __launch_bounds__(TB) void k_apply(KParams kp, const MT *__restrict__ M, const double *__restrict__ x,
+                                              const double *__restrict__ t, double *__restrict__ out) {
+  const size_t N = (size_t)kp.ncells;
+  const Groups gr = block_groups(node_groups(kp));
+  for (int grp = gr.first; grp < gr.last; grp += gr.step) {
+    int i, j, k;
+    const int g = group_node<DIM>(kp, grp, i, j, k);
+    if (g < 0) continue;
+    double xc[3], y[3];
+    apply_node<DIM, TR, MT>(kp, M, x, t, g, i, j, k, xc, y);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) out[c * N + g] = y[c];
+  }
+}
+
+// t = C_NC x of a vector of the iteration (3D; j: its column, -1 after a
+// cycle, -2 at the start)
+__global__ __launch_bounds__(TB) void k_gm_curl(KParams kp, GmBuf gm, const double *__restrict__ x, int j) {
+  if (j == -2 ? gm.st->code != 0 : (j < 0 ? tail_off(gm.st) : arnoldi_off(gm.st, j))) return;
+  const size_t N = (size_t)kp.ncells;
+  const Groups gr = block_groups(node_groups(kp));
+  for (int grp = gr.first; grp < gr.last; grp += gr.step) {
+    int i, jj, k;
+    const int g = group_node<3>(kp, grp, i, jj, k);
+    if (g < 0) continue;
+    double c[3][8], r[3];
+    load_cube<3>(kp, x, i, jj, k, c);
+    cube_curl<3>(kp, c, r);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) gm.t[q * N + g] = r[q];
+  }
+}
+
+__device__ __forceinline__ void init_state(const GmBuf &gm, int code) {
+  GmState *st = gm.st;
+  st->code = code;
+  st->done = 0;
+  st->end_at = -1;
+  st->total_it = 0;
+  st->cycle = 0;
+  st->rel = 0.0;
+}
+
+// The vectors' rows are padded to an even length for 16-byte access; the pad
+// stays 0.
+__device__ __forceinline__ void zero_pads(const GmBuf &gm) {
+  if (gm.ld == gm.n3) return;
+  for (int q = threadIdx.x; q <= gm.m; q += TB) gm.V[(size_t)q * gm.ld + gm.n3] = 0.0;
+  if (threadIdx.x == 0) gm.r[gm.n3] = 0.0;
+}
+
+// Start of the forward solve: b = E^n + c th dt C_CN B^n - 4 pi th dt Jhat,
+// x = x0, and the partial sums of b.b.  Does nothing, and stops the kernels
+// that follow, when an earlier call left an error flag.
+template <int DIM>
+__global__ __launch_bounds__(TB) void k_gm_rhs(KParams kp, GmBuf gm, const double *En, const double *Bn,
+                                               const double *J, const double *x0, double *x,
+                                               const int32_t *__restrict__ flags) {
+  __shared__ double lds[NW];
+  const bool refused = *flags != 0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) init_state(gm, refused ? kGmRefused : 0);
+  if (refused) return;
+  if (blockIdx.x == 0) zero_pads(gm);
+  const size_t N = (size_t)kp.ncells;
+  const double a = kp.c * kp.theta * kp.dt;
+  const double b = 4.0 * M_PI * kp.theta * kp.dt;
+  double acc[1] = {0.0};
+  const Groups gr = block_groups(node_groups(kp));
+  for (int grp = gr.first; grp < gr.last; grp += gr.step) {
+    int i, j, k;
+    const int g = group_node<DIM>(kp, grp, i, j, k);
+    if (g < 0) continue;
+    double c[3][8], cc[3];
+    load_cube<DIM>(kp, Bn, i - 1, j - 1, k - 1, c);
+    cube_curl<DIM>(kp, c, cc);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      const double bq = En[q * N + g] + a * cc[q] - b * J[q * N + g];
+      gm.b[q * N + g] = bq;
+      if (x != x0) x[q * N + g] = x0[q * N + g];
+      acc[0] += bq * bq;
+    }
+  }
+  put_partials<1>(acc, 1, lds, gm.p3);
+}
+
+// Start of the transposed solve: b = l_th + l_E1 / theta - c dt C_CN l_B1
+// (C_NC^T = C_CN), x = 0, r = b, and the partial sums as above.
+template <int DIM>
+__global__ __launch_bounds__(TB) void k_gm_adj_start(KParams kp, GmBuf gm, const double *__restrict__ lth,
+                                                     const double *__restrict__ lE1, const double *__restrict__ lB1,
+                                                     double *__restrict__ x, const int32_t *__restrict__ flags) {
+  __shared__ double lds[NW * 2];
+  const bool refused = *flags != 0;
+  if (blockIdx.x == 0 && threadIdx.x == 0) init_state(gm, refused ? kGmRefused : 0);
+  if (refused) return;
+  if (blockIdx.x == 0) zero_pads(gm);
+  const size_t N = (size_t)kp.ncells;
+  const double cdt = kp.c * kp.dt;
+  double acc[2] = {0.0, 0.0};
+  const Groups gr = block_groups(node_groups(kp));
+  for (int grp = gr.first; grp < gr.last; grp += gr.step) {
+    int i, j, k;
+    const int g = group_node<DIM>(kp, grp, i, j, k);
+    if (g < 0) continue;
+    double c[3][8], cc[3];
+    load_cube<DIM>(kp, lB1, i - 1, j - 1, k - 1, c);
+    cube_curl<DIM>(kp, c, cc);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      const double bq = lth[q * N + g] + lE1[q * N + g] / kp.theta - cdt * cc[q];
+      gm.b[q * N + g] = bq;
+      gm.r[q * N + g] = bq;
+      x[q * N + g] = 0.0;
+      acc[0] += bq * bq;
+    }
+  }
+  acc[1] = acc[0];
+  put_partials<2>(acc, 2, lds, gm.p3);
+}
+
+// The cycle ends with column k, whose vector's norm is hn: its last rotation.
+// One thread.
+__device__ __forceinline__ void end_cycle(GmState *st, int k, double hn) {
+  const double a = st->a, den = hypot(a, hn);
+  st->R[(size_t)k * (kMaxRestart + 1) + k] = den;
+  st->g[k] *= den > 0 ? a / den : 1.0;
+  st->end_at = k;
+}
+
+// Basis vectors are taken kQ at a time, all loads of a group before their
+// use (past the last vector a group repeats it, with results not used).
+constexpr int kQ = 4;
+
+// First half of column j: u = A w~ into V[j + 1], w~ = w / |w| with w in
+// V[j], and the partial sums of w~.u, V^T w~ and V^T u.  The norm of w, summed
+// here, first tells whether column j - 1 was the cycle's last (its residual
+// is |g| |w| / hypot(a, |w|)).  FIRST (j = 0): w is the residual r, whose norm
+// (and in the solve's first cycle the right-hand side's) is summed here.
+template <int DIM, bool TR, typename MT, int NV, bool FIRST>
+__global__ __launch_bounds__(TB, NV <= 32 ? 2 : 1) void k_gm_apply(KParams kp, GmBuf gm, const MT *__restrict__ M, int j, int cycle0) {
+  __shared__ double lds[NW * (2 * NV + 1)];
+  GmState *const st = gm.st;
+  if (arnoldi_off(st, j)) return;
+  const size_t N = (size_t)kp.ncells;
+  const bool head = blockIdx.x == 0 && threadIdx.x == 0;
+  double wn;
+  if constexpr (FIRST) {
+    get_sums(gm.p3, gm.na, 2, lds);
+    wn = sqrt(lds[1]);
+    const double bnorm = cycle0 ? sqrt(lds[0]) : st->bnorm;
+    const double tol = gm.rtol * bnorm;
+    const int code = (cycle0 && !isfinite(bnorm)) ? kGmBadRhs : (!isfinite(wn) ? kGmBadResidual : 0);
+    const bool conv = cycle0 && wn <= tol;
+    if (head) {
+      st->bnorm = bnorm;
+      st->tol = tol;
+      st->rel = bnorm > 0 ? wn / bnorm : 0.0;
+      st->g[0] = wn;
+      st->wn = wn;
+      if (code)
+        st->code = code;
+      else if (conv)
+        st->done = kGmAtStart;
+    }
+    if (code || conv) return;
+  } else {
+    get_sums(gm.p2, gm.no, 1, lds);
+    wn = sqrt(lds[0]);
+    const double den = hypot(st->a, wn);
+    const double est = den > 0 ? fabs(st->g[j - 1]) * (wn / den) : 0.0;
+    const bool bad = !isfinite(wn);
+    const bool last = est <= st->tol || wn == 0.0 || j == gm.m || st->total_it >= gm.maxit;
+    if (head) {
+      if (bad)
+        st->code = kGmBadVector;
+      else if (last)
+        end_cycle(st, j - 1, wn);
+      else
+        st->wn = wn;
+    }
+    if (bad || last) return;
+  }
+  const double inv = 1.0 / wn;
+  __syncthreads();
+  const double *const x = FIRST ? gm.r : gm.V + (size_t)j * gm.ld;
+  double *const u = gm.V + (size_t)(j + 1) * gm.ld;
+  // w~.u, then s, then z
+  double acc[2 * NV + 1];
+#pragma unroll
+  for (int q = 0; q <= 2 * NV; ++q) acc[q] = 0.0;
+  const Groups gr = block_groups(node_groups(kp));
+  for (int grp = gr.first; grp < gr.last; grp += gr.step) {
+    int i, jj, k;
+    const int g = group_node<DIM>(kp, grp, i, jj, k);
+    if (g < 0) continue;
+    double w[3], y[3];
+    apply_node<DIM, TR, MT>(kp, M, x, gm.t, g, i, jj, k, w, y);
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      w[c] *= inv;
+      y[c] *= inv;
+      u[c * N + g] = y[c];
+      acc[0] += w[c] * y[c];
+    }
+    if constexpr (!FIRST) {
+#pragma unroll
+      for (int q0 = 0; q0 < NV; q0 += kQ) {
+        if (q0 < j) {
+          double v[kQ][3];
+#pragma unroll
+          for (int q = 0; q < kQ; ++q)
+#pragma unroll
+            for (int c = 0; c < 3; ++c) v[q][c] = gm.V[(size_t)min(q0 + q, j - 1) * gm.ld + c * N + g];
+#pragma unroll
+          for (int q = 0; q < kQ; ++q) {
+            acc[1 + q0 + q] += v[q][0] * w[0] + v[q][1] * w[1] + v[q][2] * w[2];
+            acc[1 + NV + q0 + q] += v[q][0] * y[0] + v[q][1] * y[1] + v[q][2] * y[2];
+          }
+        }
+      }
+    }
+  }
+  // partial sums: w~.u, s_0 .. s_{j-1}, z_0 .. z_{j-1}
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+#pragma unroll
+  for (int q = 0; q <= (FIRST ? 0 : 2 * NV); ++q) {
+    const int k = q <= NV ? q : q - NV;  // 1 + vector
+    if (k <= j) {
+      double v = acc[q];
+#pragma unroll
+      for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
+      if (lane == 0) lds[wid * (2 * NV + 1) + (q <= NV ? q : j + k)] = v;
+    }
+  }
+  __syncthreads();
+  for (int q = threadIdx.x; q <= 2 * j; q += TB) {
+    double s = lds[q];
+#pragma unroll
+    for (int w = 1; w < NW; ++w) s += lds[w * (2 * NV + 1) + q];
+    gm.p1[(size_t)q * gridDim.x + blockIdx.x] = s;
+  }
+}
+
+struct alignas(16) D2 {
+  double x, y;
+};
+
+// Column j of the Hessenberg matrix and the rotations (one wave): s, z and
+// z_j as in k_gm_ortho, hh: room for 2 (kMaxRestart + 1) values in LDS.
+// Column j - 1 takes the correction of its vector's second pass and its final
+// rotation; column j is rotated by all of them, its last entry kept in a until
+// the norm of the next candidate is known.
+__device__ void hessenberg_column(const GmBuf &gm, int j, const double *s, const double *z, double zj, double nu,
+                                  double *hh) {
+  constexpr int LD = kMaxRestart + 1;
+  GmState *const st = gm.st;
+  const int lane = threadIdx.x & 63;
+  double *const prev = hh, *const cur = hh + LD;  // the two columns
+  const double wn = st->wn;
+  for (int k = lane; k <= j; k += 64) {
+    if (j > 0) {
+      const double h = k < j ? st->H[(size_t)(j - 1) * LD + k] + s[k] * wn : nu * wn;
+      st->H[(size_t)(j - 1) * LD + k] = h;
+      prev[k] = h;
+    }
+    double c = k < j ? z[k] : zj;
+    for (int i = k > 0 ? k - 1 : 0; i + 1 < j; ++i) c -= st->H[(size_t)i * LD + k] * s[i];
+    if (j > 0) c -= prev[k] * s[j - 1];
+    c /= nu;
+    st->H[(size_t)j * LD + k] = c;
+    cur[k] = c;
+  }
+  __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  if (lane != 0) return;
+  double a = prev[0], b = cur[0];
+  for (int k = 0; k + 1 < j; ++k) {
+    const double c = st->cs[k], sn = st->sn[k];
+    const double p = prev[k + 1], q = cur[k + 1];
+    st->R[(size_t)(j - 1) * LD + k] = c * a + sn * p;
+    a = -sn * a + c * p;
+    st->R[(size_t)j * LD + k] = c * b + sn * q;
+    b = -sn * b + c * q;
+  }
+  if (j > 0) {
+    const double hn = prev[j], den = hypot(a, hn);
+    const double c = den > 0 ? a / den : 1.0, sn = den > 0 ? hn / den : 0.0;
+    st->R[(size_t)(j - 1) * LD + j - 1] = den;
+    st->cs[j - 1] = c;
+    st->sn[j - 1] = sn;
+    const double g = st->g[j - 1];
+    st->g[j - 1] = c * g;
+    st->g[j] = -sn * g;
+    const double q = cur[j];
+    st->R[(size_t)j * LD + j - 1] = c * b + sn * q;
+    b = -sn * b + c * q;
+  }
+  st->a = b;
+  ++st->total_it;
+}
+
+// Second half of column j: v_j into V[j], the next candidate into V[j + 1],
+// and the partial sums of its square.  When nu^2 has cancelled (at most 1e-4:
+// the candidate lay in the span of the basis) the cycle ends with the column
+// before.
+__global__ __launch_bounds__(TB) void k_gm_ortho(GmBuf gm, int j) {
+  __shared__ double sums[2 * kMaxRestart + 1], s[kMaxRestart], z[kMaxRestart], hh[2 * (kMaxRestart + 1)], lds[NW];
+  GmState *const st = gm.st;
+  if (arnoldi_off(st, j)) return;
+  get_sums(gm.p1, gm.na, 2 * j + 1, sums);
+  const int jq = (j + kQ - 1) / kQ * kQ;
+  for (int q = threadIdx.x; q < jq; q += TB) {
+    s[q] = q < j ? sums[1 + q] : 0.0;
+    z[q] = q < j ? sums[1 + j + q] : 0.0;
+  }
+  __syncthreads();
+  double ss = 0.0, sz = 0.0;
+  for (int q = 0; q < j; ++q) {
+    ss += s[q] * s[q];
+    sz += s[q] * z[q];
+  }
+  const double nu2 = 1.0 - ss;
+  const double wn = st->wn;
+  if (j > 0 && !(nu2 > 1e-4)) {
+    if (blockIdx.x == 0 && threadIdx.x == 0) end_cycle(st, j - 1, wn);
+    return;
+  }
+  const double nu = sqrt(nu2);
+  const double zj = (sums[0] - sz) / nu;
+  if (blockIdx.x == 0 && threadIdx.x >= TB - 64) hessenberg_column(gm, j, s, z, zj, nu, hh);
+  const double inv = 1.0 / wn, inu = 1.0 / nu;
+  const size_t n2 = gm.ld >> 1, ld2 = gm.ld >> 1;
+  D2 *const V = reinterpret_cast<D2 *>(gm.V);
+  const D2 *const wv = j == 0 ? reinterpret_cast<const D2 *>(gm.r) : V + (size_t)j * ld2;
+  double acc[1] = {0.0};
+  for (size_t i = (size_t)blockIdx.x * TB + threadIdx.x; i < n2; i += (size_t)gridDim.x * TB) {
+    D2 w = wv[i], u = V[(size_t)(j + 1) * ld2 + i];
+    w.x *= inv;
+    w.y *= inv;
+    for (int q0 = 0; q0 < j; q0 += kQ) {
+      D2 v[kQ];
+#pragma unroll
+      for (int q = 0; q < kQ; ++q) v[q] = V[(size_t)min(q0 + q, j - 1) * ld2 + i];
+#pragma unroll
+      for (int q = 0; q < kQ; ++q) {
+        const double sq = s[q0 + q], zq = z[q0 + q];
+        w.x -= sq * v[q].x;
+        w.y -= sq * v[q].y;
+        u.x -= zq * v[q].x;
+        u.y -= zq * v[q].y;
+      }
+    }
+    w.x *= inu;
+    w.y *= inu;
+    u.x = (u.x - zj * w.x) * inu;
+    u.y = (u.y - zj * w.y) * inu;
+    V[(size_t)j * ld2 + i] = w;
+    V[(size_t)(j + 1) * ld2 + i] = u;
+    acc[0] += u.x * u.x + u.y * u.y;
+  }
+  put_partials<1>(acc, 1, lds, gm.p2);
+}
+
+// End of a cycle of n columns: y = R^-1 g (upper triangular, a column at a
+// time over the lanes of one wave) and x += V y.
+__global__ __launch_bounds__(TB) void k_gm_update(GmBuf gm, double *__restrict__ x) {
+  __shared__ double y[kMaxRestart];
+  const GmState *const st = gm.st;
+  if (tail_off(st)) return;
+  const int n = st->end_at + 1;
+  if (threadIdx.x < 64) {
+    const int lane = threadIdx.x;  // n <= 64: one row per lane
+    double g = lane < n ? st->g[lane] : 0.0;
+    for (int k = n - 1; k >= 0; --k) {
+      const double *const col = st->R + (size_t)k * (kMaxRestart + 1);
+      const double d = col[k], gk = __shfl(g, k);
+      const double yk = d != 0.0 ? gk / d : 0.0;
+      if (lane == k) y[k] = yk;
+      if (lane < k) g -= col[lane] * yk;
+    }
+  }
+  __syncthreads();
+  for (size_t i = (size_t)blockIdx.x * TB + threadIdx.x; i < gm.n3; i += (size_t)gridDim.x * TB) {
+    double xi = x[i];
+#pragma unroll 8
+    for (int q = 0; q < n; ++q) xi += y[q] * gm.V[(size_t)q * gm.ld + i];
+    x[i] = xi;
+  }
+}
+
+// r = b - A x and the partial sums of r.r (beside those of b.b), at the
+// start or after a cycle
+template <int DIM, bool TR, typename MT>
+__global__ __launch_bounds__(TB) void k_gm_residual(KParams kp, GmBuf gm, const MT *__restrict__ M,
+                                                    const double *__restrict__ x, int start) {
+  __shared__ double lds[NW];
+  if (start ? gm.st->code != 0 : tail_off(gm.st)) return;
+  const size_t N = (size_t)kp.ncells;
+  double acc[1] = {0.0};
+  const Groups gr = block_groups(node_groups(kp));
+  for (int grp = gr.first; grp < gr.last; grp += gr.step) {
+    int i, j, k;
+    const int g = group_node<DIM>(kp, grp, i, j, k);
+    if (g < 0) continue;
+    double xc[3], y[3];
+    apply_node<DIM, TR, MT>(kp, M, x, gm.t, g, i, j, k, xc, y);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      const double rq = gm.b[q * N + g] - y[q];
+      gm.r[q * N + g] = rq;
+      acc[0] += rq * rq;
+    }
+  }
+  put_partials<1>(acc, 1, lds, gm.p3 + gridDim.x);
+}
+
+// The true residual's test.  True when the solve has ended (converged, at
+// the start or now, or at its iteration limit) and the caller's update is
+// due; else a new cycle starts.  Every block takes the same decision; block
+// 0 records it.
+__device__ __forceinline__ bool solve_ended(const GmBuf &gm, double *lds) {
+  GmState *const st = gm.st;
+  const int done0 = st->done;
+  if (st->code != 0) return false;
+  if (done0 == kGmAtStart) return true;
+  if (st->end_at < 0) return false;
+  get_sums(gm.p3 + gm.na, gm.na, 1, lds);
+  const double beta = sqrt(lds[0]);
+  const double bnorm = st->bnorm;
+  const bool bad = !isfinite(beta);
+  const bool conv = beta <= st->tol;
+  const bool ended = !bad && (conv || st->total_it >= gm.maxit);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    st->rel = bnorm > 0 ? beta / bnorm : 0.0;
+    if (bad)
+      st->code = kGmBadResidual;
+    else if (ended)
+      st->done = conv ? kGmConverged : kGmAtLimit;
+    else {
+      st->end_at = -1;
+      ++st->cycle;
+    }
+  }
+  return ended;
+}
+
+// End of the forward solve: the test, then B^{n+1} = B^n - c dt C_NC E_th and
+// E^{n+1} = (E_th - (1 - th) E^n) / th.
+template <int DIM>
+__global__ __launch_bounds__(TB) void k_gm_finish(KParams kp, GmBuf gm, const double *En, const double *Bn,
+                                                  const double *__restrict__ Eth, double *En1, double *Bn1) {
+  __shared__ double lds[1];
+  if (!solve_ended(gm, lds)) return;
+  const size_t N = (size_t)kp.ncells;
+  const double th = kp.theta;
+  const Groups gr = block_groups(node_groups(kp));
+  for (int grp = gr.first; grp < gr.last; grp += gr.step) {
+    int i, j, k;
+    const int g = group_node<DIM>(kp, grp, i, j, k);
+    if (g < 0) continue;
+    double c[3][8], cc[3];
+    load_cube<DIM>(kp, Eth, i, j, k, c);
+    cube_curl<DIM>(kp, c, cc);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      Bn1[q * N + g] = Bn[q * N + g] - kp.c * kp.dt * cc[q];
+      En1[q * N + g] = (Eth[q * N + g] - (1.0 - th) * En[q * N + g]) / th;
+    }
+  }
+}
+
+// End of the transposed solve: the test, then l_En += -(1 - th)/th l_E1 + mu
+// and l_Bn += l_B1 + c th dt C_NC mu (C_CN^T = C_NC).
+template <int DIM>
+__global__ __launch_bounds__(TB) void k_gm_adj_finish(KParams kp, GmBuf gm, const double *lE1, const double *lB1,
+                                                      const double *__restrict__ mu, double *lEn, double *lBn) {
+  __shared__ double lds[1];
+  if (!solve_ended(gm, lds)) return;
+  const size_t N = (size_t)kp.ncells;
+  const double th = kp.theta, ctdt = kp.c * kp.theta * kp.dt;
+  const Groups gr = block_groups(node_groups(kp));
+  for (int grp = gr.first; grp < gr.last; grp += gr.step) {
+    int i, j, k;
+    const int g = group_node<DIM>(kp, grp, i, j, k);
+    if (g < 0) continue;
+    double c[3][8], cc[3];
+    load_cube<DIM>(kp, mu, i, j, k, c);
+    cube_curl<DIM>(kp, c, cc);
+#pragma unroll
+    for (int q = 0; q < 3; ++q) {
+      lEn[q * N + g] += -(1.0 - th) / th * lE1[q * N + g] + mu[q * N + g];
+      lBn[q * N + g] += lB1[q * N + g] + ctdt * cc[q];
+    }
+  }
+}
+
+
+// KERNEL(DIM, TR, MT) for the solve's dimension, transposition and M's type
+#define RELSIM_GM_MASS(KERNEL)                                   \
+  do {                                                           \
+    if (kp.dim == 2) {                                           \
+      if (transpose) {                                           \
+        if (mass_fp32) KERNEL(2, true, float);                   \
+        else KERNEL(2, true, double);                            \
+      } else {                                                   \
+        if (mass_fp32) KERNEL(2, false, float);                  \
+        else KERNEL(2, false, double);                           \
+      }                                                          \
+    } else {                                                     \
+      if (transpose) {                                           \
+        if (mass_fp32) KERNEL(3, true, float);                   \
+        else KERNEL(3, true, double);                            \
+      } else {                                                   \
+        if (mass_fp32) KERNEL(3, false, float);                  \
+        else KERNEL(3, false, double);                           \
+      }                                                          \
+    }                                                            \
+  } while (0)
+
+template <int DIM, bool TR, typename MT>
+void gm_apply(const KParams &kp, const GmBuf &gm, const void *Mv, int j, bool cycle0, int nb, hipStream_t st) {
+  const MT *M = static_cast<const MT *>(Mv);
+  if (j == 0)
+    hipLaunchKernelGGL((k_gm_apply<DIM, TR, MT, 1, true>), dim3(nb), dim3(TB), 0, st, kp, gm, M, j, cycle0 ? 1 : 0);
+  else if (j <= 8)
+    hipLaunchKernelGGL((k_gm_apply<DIM, TR, MT, 8, false>), dim3(nb), dim3(TB), 0, st, kp, gm, M, j, 0);
+  else if (j <= 16)
+    hipLaunchKernelGGL((k_gm_apply<DIM, TR, MT, 16, false>), dim3(nb), dim3(TB), 0, st, kp, gm, M, j, 0);
+  else if (j <= 32)
+    hipLaunchKernelGGL((k_gm_apply<DIM, TR, MT, 32, false>), dim3(nb), dim3(TB), 0, st, kp, gm, M, j, 0);
+  else
+    hipLaunchKernelGGL((k_gm_apply<DIM, TR, MT, 64, false>), dim3(nb), dim3(TB), 0, st, kp, gm, M, j, 0);
+}
+
+void gm_residual(const KParams &kp, const GmBuf &gm, int mass_fp32, bool transpose, const void *M, const double *x,
+                 bool start, hipStream_t st) {
+  const int nb = gm.na;
+  if (kp.dim == 3) hipLaunchKernelGGL(k_gm_curl, dim3(nb), dim3(TB), 0, st, kp, gm, x, start ? -2 : -1);
+#define RELSIM_RES(DIM, TR, MT)                                                                                       \
+  hipLaunchKernelGGL((k_gm_residual<DIM, TR, MT>), dim3(nb), dim3(TB), 0, st, kp, gm, static_cast<const MT *>(M), x, \
+                     start ? 1 : 0)
+  RELSIM_GM_MASS(RELSIM_RES);
+#undef RELSIM_RES
+}
+
+}  // namespace
+
+void launch_apply(const KParams &kp, int mass_fp32, bool transpose, const void *M, const double *x, const double *t,
+                  double *out, hipStream_t st) {
+  const int ng = node_groups(kp);
+#define RELSIM_APPLY(DIM, TR, MT)                                                               \
+  hipLaunchKernelGGL((k_apply<DIM, TR, MT>), dim3(ng), dim3(TB), 0, st, kp, static_cast<const MT *>(M), x, t, out)
+  RELSIM_GM_MASS(RELSIM_APPLY);
+#undef RELSIM_APPLY
+}
+
+void gm_blocks(const KParams &kp, GmBuf &gm) {
+  const int ng = node_groups(kp);
+  gm.na = ng < kGmNodeBlocks ? ng : kGmNodeBlocks;
+  const size_t nv = (gm.ld / 2 + TB - 1) / TB;
+  gm.no = nv < (size_t)kGmVecBlocks ? (int)nv : kGmVecBlocks;
+}
+
+void launch_gm_start(const KParams &kp, const GmBuf &gm, int mass_fp32, const void *M, const double *En,
+                     const double *Bn, const double *J, const double *x0, double *x, const int32_t *flags,
+                     hipStream_t st) {
+  const int nb = gm.na;
+  if (kp.dim == 2)
+    hipLaunchKernelGGL(k_gm_rhs<2>, dim3(nb), dim3(TB), 0, st, kp, gm, En, Bn, J, x0, x, flags);
+  else
+    hipLaunchKernelGGL(k_gm_rhs<3>, dim3(nb), dim3(TB), 0, st, kp, gm, En, Bn, J, x0, x, flags);
+  gm_residual(kp, gm, mass_fp32, false, M, x, true, st);
+}
+
+void launch_gm_adj_start(const KParams &kp, const GmBuf &gm, const double *lth, const double *lE1, const double *lB1,
+                         double *x, const int32_t *flags, hipStream_t st) {
+  const int nb = gm.na;
+  if (kp.dim == 2)
+    hipLaunchKernelGGL(k_gm_adj_start<2>, dim3(nb), dim3(TB), 0, st, kp, gm, lth, lE1, lB1, x, flags);
+  else
+    hipLaunchKernelGGL(k_gm_adj_start<3>, dim3(nb), dim3(TB), 0, st, kp, gm, lth, lE1, lB1, x, flags);
+}
+
+void launch_gm_apply(const KParams &kp, const GmBuf &gm, int mass_fp32, bool transpose, const void *M, int j,
+                     bool cycle0, hipStream_t st) {
+  const int nb = gm.na;
+  if (kp.dim == 3)
+    hipLaunchKernelGGL(k_gm_curl, dim3(nb), dim3(TB), 0, st, kp, gm, j == 0 ? gm.r : gm.V + (size_t)j * gm.ld, j);
+#define RELSIM_STEP(DIM, TR, MT) gm_apply<DIM, TR, MT>(kp, gm, M, j, cycle0, nb, st)
+  RELSIM_GM_MASS(RELSIM_STEP);
+#undef RELSIM_STEP
+}
+
+void launch_gm_ortho(const GmBuf &gm, int j, hipStream_t st) {
+  hipLaunchKernelGGL(k_gm_ortho, dim3(gm.no), dim3(TB), 0, st, gm, j);
+}
+
+void launch_gm_update(const GmBuf &gm, double *x, hipStream_t st) {
+  hipLaunchKernelGGL(k_gm_update, dim3(gm.no), dim3(TB), 0, st, gm, x);
+}
+
+void launch_gm_residual(const KParams &kp, const GmBuf &gm, int mass_fp32, bool transpose, const void *M,
+                        const double *x, hipStream_t st) {
+  gm_residual(kp, gm, mass_fp32, transpose, M, x, false, st);
+}
+
+void launch_gm_finish(const KParams &kp, const GmBuf &gm, const double *En, const double *Bn, const double *Eth,
+                      double *En1, double *Bn1, hipStream_t st) {
+  const int nb = node_groups(kp);
+  if (kp.dim == 2)
+    hipLaunchKernelGGL(k_gm_finish<2>, dim3(nb), dim3(TB), 0, st, kp, gm, En, Bn, Eth, En1, Bn1);
+  else
+    hipLaunchKernelGGL(k_gm_finish<3>, dim3(nb), dim3(TB), 0, st, kp, gm, En, Bn, Eth, En1, Bn1);
+}
+
+void launch_gm_adj_finish(const KParams &kp, const GmBuf &gm, const double *lE1, const double *lB1, const double *mu,
+                          double *lEn, double *lBn, hipStream_t st) {
+  const int nb = node_groups(kp);
+  if (kp.dim == 2)
+    hipLaunchKernelGGL(k_gm_adj_finish<2>, dim3(nb), dim3(TB), 0, st, kp, gm, lE1, lB1, mu, lEn, lBn);
+  else
+    hipLaunchKernelGGL(k_gm_adj_finish<3>, dim3(nb), dim3(TB), 0, st, kp, gm, lE1, lB1, mu, lEn, lBn);
+}
+
+}  // namespace relsim

@@ -30,12 +30,14 @@ struct KParams {
 
 // Offsets (in bytes) of the regions carved out of the caller's workspace.
 struct Layout {
-  size_t S, cnt, pre, total, scan_tmp, dirc, err, gm_V, gm_t, gm_b, gm_r, gm_part, gm_small, red_part;
+  size_t S, cnt, pre, total, scan_tmp, dirc, err, gm_V, gm_t, gm_b, gm_r, gm_part, gm_state, red_part, red_res;
   size_t gs_k0, gs_k1, gs_v0, gs_v1, gs_hist, stB, stE, sink, kin_part, push_ke, end;
 };
 
 constexpr int kMaxRestart = 64;
-constexpr int kDotBlocks = 1024;    // blocks of the multi-dot reduction
+constexpr int kGmThreads = 256;     // threads per block of the GMRES kernels
+constexpr int kGmNodeBlocks = 512;  // most blocks of the per-node GMRES kernels (a multiple of 8)
+constexpr int kGmVecBlocks = 512;   // most blocks of the others
 constexpr int kRedBlocks = 1024;    // blocks of the energy reductions
 constexpr int kSinkSlots = 512;     // per-lane store sinks of the particle kernels (power of two), 32 B each
 
@@ -79,7 +81,7 @@ __host__ __device__ constexpr int m_centre() { return DIM == 3 ? 13 : 4; }
 // earlier.  The chunks in flight stay within kStrip planes.  In 2D it is the
 // plain order.  Blocks of 256 threads take 4 chunks.
 constexpr int kStrip = 4;
-inline int grid_node_blocks(int nx, int ny, int nz) { return (((nx + 63) >> 6) * ny * nz + 3) >> 2; }
+__host__ __device__ inline int grid_node_blocks(int nx, int ny, int nz) { return (((nx + 63) >> 6) * ny * nz + 3) >> 2; }
 // chunk L (of the grid's ((nx + 63) / 64) ny nz), lane in [0, 64) -> node
 // (i, j, k) and its linear index, or -1 past the grid
 __device__ __forceinline__ int strip_node(int nx, int ny, int nz, int L, int lane, int &i, int &j, int &k) {
@@ -181,38 +183,70 @@ void launch_push_adjoint(const KParams &kp, const AdjInPtrs &in, int n, const do
                          double *lu_out, double *lEth, double *lB, hipStream_t st);
 void launch_deposit_adjoint(const KParams &kp, const AdjInPtrs &in, int n, const double *B, const double *Eth,
                             const double *mu, double *lx_out, double *lu_out, double *lB, hipStream_t st);
-void launch_adj_rhs(size_t n3, double theta, double cdt, const double *lth, const double *lE1, const double *ccn_lB1,
-                    double *out, hipStream_t st);
-void launch_adj_finish(size_t n3, double theta, double ctdt, const double *lE1, const double *lB1, const double *mu,
-                       const double *cnc_mu, double *lEn, double *lBn, hipStream_t st);
 
 // ---- field kernels (field.hip) ----
 void launch_curl(const KParams &kp, const double *in, double *out, int to_centres, hipStream_t st);
-// M: the stored half of the mass matrix, float if mass_fp32, else double
-void launch_apply_A_tail(const KParams &kp, int mass_fp32, const void *M, const double *x, const double *t,
-                         double *out, hipStream_t st);
-void launch_apply_AT_tail(const KParams &kp, int mass_fp32, const void *M, const double *x, const double *t,
-                          double *out, hipStream_t st);
-void launch_rhs(const KParams &kp, const double *En, const double *Bn, const double *J, double *out, hipStream_t st);
-void launch_field_update(const KParams &kp, const double *En, const double *Bn, const double *Eth, double *En1,
-                         double *Bn1, hipStream_t st);
-// out[k] = sum_i V[k][i] * w[i] for k < nvec (V rows of length n with stride ld)
-// written to partials[blocks][nvec]; then reduced into res[nvec] (device).
-void launch_mdot(const double *V, size_t ld, int nvec, const double *w, size_t n, double *partials, double *res,
-                 hipStream_t st);
-// w -= sum_k h[k] V[k]  (h on the device)
-void launch_maxpy(const double *V, size_t ld, int nvec, const double *h, double *w, size_t n, hipStream_t st);
-// w -= sum_k h[k] V[k] (k < nvec), then res[0..nvec] = (V[k] . w for k <
-// nvec, w . w), reading the basis once; returns 0 (and launches nothing)
-// for nvec > 32, where the caller takes launch_maxpy and launch_mdot.
-int launch_maxpy_dot(const double *V, size_t ld, int nvec, const double *h, double *w, size_t n, double *partials,
-                     double *res, hipStream_t st);
-// w = (w - sum_k h[k] V[k]) / hn, hn = sqrt(h[nvec] - sum_k h[k]^2), left
-// unscaled when that difference is at most 1e-4 h[nvec]; h[nvec + 1] = hn,
-// or 0 when unscaled
-void launch_maxpy_scale(const double *V, size_t ld, int nvec, double *h, double *w, size_t n, hipStream_t st);
-// y = a * x + b * y  (scalars from the host)
-void launch_axpby(double a, const double *x, double b, double *y, size_t n, hipStream_t st);
+
+// ---- GMRES kernels (gmres.hip) ----
+// State of a solve, on the device.  Its head is what the host reads.
+enum GmCode { kGmRefused = 1, kGmBadRhs, kGmBadResidual, kGmBadVector };  // why the solve stopped without a result
+enum GmDone { kGmAtStart = 1, kGmConverged, kGmAtLimit };                 // how it ended
+struct GmHead {
+  double rel;         // the last true relative residual
+  int32_t code;       // GmCode, or 0
+  int32_t done;       // GmDone, or 0
+  int32_t end_at;     // the column that ended the cycle, or -1
+  int32_t total_it;   // Arnoldi steps so far
+  int32_t cycle;      // cycles that ended without ending the solve
+};
+struct GmState : GmHead {
+  double bnorm, tol;
+  double wn;                                   // norm of the column's candidate vector
+  double a;                                    // last rotated entry of the newest column
+  double g[kMaxRestart + 1];                   // the rotated right-hand side
+  double cs[kMaxRestart], sn[kMaxRestart];     // the rotations
+  // the Hessenberg matrix and its rotated form, column k at k (kMaxRestart + 1)
+  double H[kMaxRestart * (kMaxRestart + 1)], R[kMaxRestart * (kMaxRestart + 1)];
+};
+// The solve's buffers: V [m + 1] rows of n3 values with stride ld (even; the
+// pad is 0), vectors t, b, r; partial sums per block, [quantity][block]: p1
+// (2 kMaxRestart + 1 quantities) and p3 (2) by the per-node kernels, p2 (1)
+// by ortho.
+struct GmBuf {
+  double *V, *t, *b, *r, *p1, *p2, *p3;
+  GmState *st;
+  size_t n3, ld;
+  int na, no;  // blocks of the per-node kernels, and of ortho and update
+  int m, maxit;
+  double rtol;
+};
+// out = A x or A^T x, with t = C_NC x given in 3D (not read in 2D); M: the
+// stored half of the mass matrix, float if mass_fp32, else double
+void launch_apply(const KParams &kp, int mass_fp32, bool transpose, const void *M, const double *x, const double *t,
+                  double *out, hipStream_t st);
+// A solve is start (or adj_start), then apply(0), ortho(0), apply(1), ortho(1),
+// ..., apply(n) for n columns (apply(n) finds that column n - 1 was the last),
+// then update, residual and finish (or adj_finish).  Kernels past the end of
+// the cycle or of the solve do nothing, so more may be enqueued than are
+// needed; the head of the state says how far the solve came.
+void gm_blocks(const KParams &kp, GmBuf &gm);  // sets na, no
+void launch_gm_start(const KParams &kp, const GmBuf &gm, int mass_fp32, const void *M, const double *En,
+                     const double *Bn, const double *J, const double *x0, double *x, const int32_t *flags,
+                     hipStream_t st);
+void launch_gm_adj_start(const KParams &kp, const GmBuf &gm, const double *lth, const double *lE1, const double *lB1,
+                         double *x, const int32_t *flags, hipStream_t st);
+void launch_gm_apply(const KParams &kp, const GmBuf &gm, int mass_fp32, bool transpose, const void *M, int j,
+                     bool cycle0, hipStream_t st);
+void launch_gm_ortho(const GmBuf &gm, int j, hipStream_t st);
+void launch_gm_update(const GmBuf &gm, double *x, hipStream_t st);
+void launch_gm_residual(const KParams &kp, const GmBuf &gm, int mass_fp32, bool transpose, const void *M,
+                        const double *x, hipStream_t st);
+void launch_gm_finish(const KParams &kp, const GmBuf &gm, const double *En, const double *Bn, const double *Eth,
+                      double *En1, double *Bn1, hipStream_t st);
+void launch_gm_adj_finish(const KParams &kp, const GmBuf &gm, const double *lE1, const double *lB1, const double *mu,
+                          double *lEn, double *lBn, hipStream_t st);
+
+// ---- fixed-order reductions (field.hip) ----
 void launch_sumsq_partials(const double *x, size_t n, double *partials, hipStream_t st);
 void launch_reduce_partials(const double *partials, int nparts, int nvec, double *res, hipStream_t st);
 // res[0] = sum of in[0..n) in a fixed order (tmp: kRedBlocks doubles)
