@@ -156,6 +156,34 @@ int validate(const relsim_params *p, std::string &msg) {
 // Stride of the Krylov basis's rows: even, for 16-byte access.
 size_t gm_stride(size_t n3) { return (n3 + 1) & ~(size_t)1; }
 
+// Rows of the push passes' tiles (about 16 cells wide): 32 in 2D, 16 in 3D,
+// fewer where a tile's particles take more than 512 KiB.  An XCD works on
+// several tiles at a time, and their particles and destinations share its 4
+// MiB of L2 (200 x 102 sheet, 512 FP64 particles per cell: 380 us with 34
+// rows, 376 up to 1 to 4 MiB, 371 up to 512 KiB; 317 x 211, 80 per cell: 163
+// -> 159 us; the sheets below keep their times).
+int push_tile_rows(const relsim_params *p) {
+  const double nc = (double)p->nx * p->ny * (p->dim == 3 ? p->nz : 1);
+  const double row = 16.0 * (p->dim == 3 ? 4 : 1) * (double)p->max_particles / nc *
+                     (p->dim == 3 ? 8 : 6) * (p->precision == RELSIM_MIXED ? 4 : 8);
+  int rows = p->dim == 3 ? 16 : 32;
+  while (rows > 1 && rows * row > (double)(1 << 19)) rows /= 2;
+  return rows;
+}
+
+// Most waves of a push pass: segments of one cell, in the tiles that
+// make_kparams and the push passes choose.
+size_t max_push_waves(const relsim_params *p) {
+  auto padded = [](int n, int cap) {
+    const int t = even_tile(n, cap);
+    return (size_t)((n + t - 1) / t) * t;
+  };
+  size_t most = 0;
+  for (int C = 1; C <= 64; C *= 2)  // segments side by side in a tile: 16 / C
+    most = std::max(most, padded((p->nx + C - 1) / C, C < 16 ? 16 / C : 1));
+  return most * padded(p->ny, push_tile_rows(p)) * (p->dim == 3 ? padded(p->nz, 4) : 1);
+}
+
 Layout make_layout(const relsim_params *p) {
   Layout L{};
   const size_t nc = (size_t)p->nx * p->ny * (p->dim == 3 ? p->nz : 1);
@@ -195,7 +223,7 @@ Layout make_layout(const relsim_params *p) {
   L.stE = take(ng * 4 * es);
   L.sink = take((size_t)kSinkSlots * 64 * 32);
   L.kin_part = take(nc * 8);
-  L.push_ke = take(nc * 8);
+  L.push_ke = take((size_t)max_push_waves(p) * 8);
   L.end = o;
   return L;
 }
@@ -228,9 +256,11 @@ KParams make_kparams(const relsim_params *p) {
   // 3D 16 rows x 4 layers): the re-sort then writes each destination bin's
   // runs from the rows above and below it closer together in time, so more
   // of its partly written lines are completed in L2 before they go to HBM
-  // (measured against 8 to 512 rows: 5-6 % off the scatter on both grids)
-  k.sty = tile(k.ny, p->dim == 3 ? 16 : 32);
-  k.stz = p->dim == 3 ? tile(k.nz, 4) : 1;
+  // (measured against 8 to 512 rows: 5-6 % off the scatter on both grids).
+  // Extents that the height does not divide are cut into equal tiles of
+  // about that height, the last of which may reach past the grid.
+  k.sty = even_tile(k.ny, push_tile_rows(p));
+  k.stz = p->dim == 3 ? even_tile(k.nz, 4) : 1;
   auto lg = [](int v) {
     int l = 0;
     while ((1 << l) < v) ++l;
@@ -276,20 +306,24 @@ KParams make_kparams(const relsim_params *p) {
 
 enum KernelKind { K_DEPOSIT, K_PUSH, K_SCATTER, K_OTHER };
 
-// Cells per wave of the push passes: the widest power of two dividing nx
-// whose segment holds about `rounds` rounds of 64 particles, while the grid
-// still gives 2048 waves and the segment's LDS stays within 8 KB (more
-// starts to limit occupancy).  The counting pass wants 8 rounds, the
-// pushing scatter 4: measured on the 1024 x 512 sheet (128 particles per
-// cell: segments of 4 and 2 cells) and the 256 x 128 x 128 sheet (16 per
-// cell: 16 cells, LDS-bound, for both).
+// Cells per wave of the push passes: the widest power of two up to nx whose
+// segment holds about `rounds` rounds of 64 particles, while the grid still
+// gives 2048 waves and the segment's LDS stays within 8 KB (more starts to
+// limit occupancy).  The counting pass wants 8 rounds, the pushing scatter 4:
+// measured on the 1024 x 512 sheet (128 particles per cell: segments of 4 and
+// 2 cells) and the 256 x 128 x 128 sheet (16 per cell: 16 cells, LDS-bound,
+// for both).  The segments need not divide the row (its last one is shorter):
+// on the 625 x 625 sheet (42 per cell on average), whose rows only single
+// cells divide, segments of 8 and 4 cells took push and re-sort from 897 to
+// 745 us (8 and 8: 945, 16 and 4: 860), and on 91 x 47 x 33 cells from 658 to
+// 274 us.
 int choose_cells(const relsim_ctx *c, int64_t n, KernelKind k) {
   const double rounds = k == K_SCATTER ? 4.0 : 8.0;
   const size_t lds = 8192;
   const double mean = (double)n / (double)c->kp.ncells;
   int C = 1;
-  while (C < 64 && 2.0 * C * mean <= rounds * 64.0 && c->kp.nx % (2 * C) == 0 &&
-         c->kp.ncells / (2 * C) >= 2048 && push_lds_bytes(c->kp, c->p.precision, 2 * C) <= lds)
+  while (C < 64 && 2.0 * C * mean <= rounds * 64.0 && 2 * C <= c->kp.nx && c->kp.ncells / (2 * C) >= 2048 &&
+         push_lds_bytes(c->kp, c->p.precision, 2 * C) <= lds)
     C *= 2;
   return C;
 }
@@ -608,7 +642,7 @@ int relsim_push_ec(relsim_ctx *c, relsim_particles *pt, const double *E_theta, c
     rc = launch_status(c, "relsim_push");
     if (rc) return rc;
     swap_sets(pt);
-    c->push_ke_parts = c->kp.ncells / cells_s;
+    c->push_ke_parts = push_waves(c->kp, cells_s);
     return RELSIM_OK;
   }
   c->push_ke_parts = 0;

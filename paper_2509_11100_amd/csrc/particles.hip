@@ -40,9 +40,20 @@
 namespace relsim {
 namespace {
 
+// Consecutive workgroups are dispatched to the 8 XCDs round robin.  Remapped
+// so that an XCD (and its L2) works through chunks of `chunk` consecutive
+// work items, the chunks going round the XCDs: neighbouring items share an
+// L2, and a band of the grid that holds more particles than the rest is
+// spread over all XCDs.  Items past the last whole round of chunks keep their
+// place.
+__device__ __forceinline__ int xcd_chunk(int b, int nb, int chunk) {
+  const int round = chunk << 3;
+  if (b >= nb / round * round) return b;
+  const int i = b >> 3, c = i / chunk;
+  return (c * 8 + (b & 7)) * chunk + (i - c * chunk);
+}
+
 __device__ __forceinline__ int xcd_remap(int b, int nb) {
-  // Consecutive workgroups are dispatched to the 8 XCDs round robin; remap so
-  // that each XCD (and its L2) works on one contiguous slice of the grid.
   const int q = nb >> 3;
   if (b >= (q << 3)) return b;
   return (b & 7) * q + (b >> 3);
@@ -394,6 +405,11 @@ __device__ __forceinline__ T inv_gbar(const KParams &kp, const PC<T> &pc, const 
     return kp.nonrel ? T(1) : rsqrt_t(T(1) + (ux * ux + uy * uy + uz * uz) * pc.invc2);
 }
 
+// An XCD takes 512 cells (4 tiles) at a time in the 2D deposit: 8 G blocks of
+// 64 / G cells.  One band per XCD leaves most of the particles of a sheet to
+// two XCDs (625 x 625 reconnection sheet: 282 -> 263 us mixed, 515 -> 467 us
+// FP64; evenly filled sheets unchanged; 2048 cells at a time 316 us).
+constexpr int kXcdDeposit = 8;
 // ---------------------------------------------------------------------------
 // S1-S3: per-cell moments
 // ---------------------------------------------------------------------------
@@ -412,7 +428,7 @@ __global__ __launch_bounds__(64) void k_deposit_cells(KParams kp, const int32_t 
   __shared__ V4<T> bsh[64 / G][9];
   __shared__ T stab[2][8];
   const int lane = threadIdx.x, grp = lane / G, gl = lane % G;
-  const int blk = xcd_remap(blockIdx.x, gridDim.x);
+  const int blk = xcd_chunk(blockIdx.x, gridDim.x, kXcdDeposit * G);
   const CellSpan cs = slot_span<G>(kp, bin_start, blk, grp);
   const PC<T> pc(kp);
 
@@ -836,7 +852,8 @@ __device__ __forceinline__ void push_one(const KParams &kp, const PC<T> &pc, con
 
 // ---------------------------------------------------------------------------
 // Push passes: a flat walk over a row segment.
-// A wave owns C consecutive cells of one grid row (C divides nx) and walks
+// A wave owns C consecutive cells of one grid row (the row's last segment
+// may be shorter) and walks
 // their particles, contiguous in memory because they are sorted by bin, 64
 // at a time across cell boundaries.  Lanes are not tied to a cell, so a cell
 // holding more particles than the others costs no idle lanes (with a lane
@@ -857,6 +874,36 @@ struct Segment {
   int *binb;         // nb + 1 bin starts, then INT_MAX up to a power of two
   int *keys;         // nb x NDIR counters (counting pass) or run bases (scatter)
 };
+
+// How the push passes' segments of C cells (the last one of a row may be
+// shorter) tile the grid: spr segments side by side in a tile, ntx x nty x
+// ntz tiles of spr x sty x stz segments (see make_kparams), the last ones
+// possibly reaching past the grid.
+struct SegTiles {
+  int spr, ntx, nty, ntz;
+  __host__ __device__ SegTiles(const KParams &kp, int C) {
+    const int nseg = (kp.nx + C - 1) / C;
+    spr = even_tile(nseg, C < 16 ? 16 / C : 1);
+    ntx = (nseg + spr - 1) / spr;
+    nty = (kp.ny + kp.sty - 1) / kp.sty;
+    ntz = (kp.nz + kp.stz - 1) / kp.stz;
+  }
+};
+// The wave's place in that order: an XCD takes up to 4 tiles at a time (a
+// fourth of its tiles on small grids).  With one contiguous band per XCD
+// instead, the rows of a current sheet, which hold most of the particles of
+// the 625 x 625 reconnection run, fall to two XCDs: push and re-sort 745 us
+// there, 635 with 4 tiles at a time (1, 2, 16, 64: 640, 640, 660, 730); 2618,
+// 2520 (2535, 2510, 2600, 2658) on the 256 x 128 x 128 sheet.
+__device__ __forceinline__ int segment_wave(const KParams &kp, int C, int b, int nb) {
+  const SegTiles t(kp, C);
+  const int tiles = t.ntx * t.nty * t.ntz >> 5;
+  return xcd_chunk(b, nb, (tiles < 1 ? 1 : (tiles < 4 ? tiles : 4)) * t.spr * kp.sty * kp.stz);
+}
+__host__ inline int segment_waves(const KParams &kp, int C) {
+  const SegTiles t(kp, C);
+  return t.ntx * t.spr * t.nty * kp.sty * t.ntz * kp.stz;
+}
 
 // Smallest power of two >= nb (nb >= 1).
 __host__ __device__ constexpr int pow2_at_least(int nb) {
@@ -884,20 +931,24 @@ __device__ __forceinline__ Segment<T, DIM> stage_segment(const KParams &kp, int 
                                                          unsigned char *smem, int lane) {
   Segment<T, DIM> sg;
   const int S = kp.nspecies;
-  sg.C = C;
-  sg.nb = C * S;
-  // segments are visited tile by tile (tiles of max(tx, C) x sty x stz cells,
+  // segments are visited tile by tile (tiles of about 16 x sty x stz cells,
   // segments row-major inside a tile), as the other particle kernels visit
   // cells: the destinations of neighbouring sources are then written close
   // together in time
-  const int TX = C > kp.tx ? C : kp.tx;
-  const int spr = TX / C, per_tile = spr * kp.sty * kp.stz;
+  const SegTiles tl(kp, C);
+  const int per_tile = tl.spr * kp.sty * kp.stz;
   const int tile = wave / per_tile, r = wave - tile * per_tile;
-  const int ntx = kp.nx / TX, nty = kp.ny / kp.sty;
-  const int t2 = tile / ntx;
-  sg.i0 = (tile - t2 * ntx) * TX + (r % spr) * C;
-  sg.j = (t2 % nty) * kp.sty + (r / spr) % kp.sty;
-  sg.k = DIM == 3 ? (t2 / nty) * kp.stz + r / (spr * kp.sty) : 0;
+  const int t2 = tile / tl.ntx;
+  sg.i0 = ((tile - t2 * tl.ntx) * tl.spr + r % tl.spr) * C;
+  sg.j = (t2 % tl.nty) * kp.sty + (r / tl.spr) % kp.sty;
+  sg.k = DIM == 3 ? (t2 / tl.nty) * kp.stz + r / (tl.spr * kp.sty) : 0;
+  // places of the last tiles outside the grid hold no cells; the last
+  // segment of a row is shorter when C does not divide nx
+  const bool inside = sg.i0 < kp.nx && sg.j < kp.ny && sg.k < kp.nz;
+  C = !inside ? 0 : (C < kp.nx - sg.i0 ? C : kp.nx - sg.i0);
+  sg.C = C;
+  sg.nb = C * S;
+  if (!inside) return sg;
   sg.c0 = sg.i0 + kp.nx * (sg.j + kp.ny * sg.k);
   const int W = C + 2, nB = W * 3 * (DIM == 3 ? 3 : 1), nE = (C + 1) * 2 * (DIM == 3 ? 2 : 1);
   sg.Bg = reinterpret_cast<V4<T> *>(smem);
@@ -1030,8 +1081,9 @@ __global__ __launch_bounds__(64) void k_push(KParams kp, int C, const int32_t *_
   extern __shared__ __attribute__((aligned(32))) unsigned char smem[];
   const int lane = threadIdx.x;
   const PC<T> pc(kp);
-  const Segment<T, DIM> sg =
-      stage_segment<T, DIM>(kp, C, xcd_remap(blockIdx.x, gridDim.x), pc, bin_start, Es, Bs, smem, lane);
+  const int wave = segment_wave(kp, C, blockIdx.x, gridDim.x);
+  const Segment<T, DIM> sg = stage_segment<T, DIM>(kp, C, wave, pc, bin_start, Es, Bs, smem, lane);
+  if (sg.C == 0) return;
   if constexpr (COUNT)
     for (int t = lane; t < sg.nb * NDIR; t += 64) sg.keys[t] = 0;
   __syncthreads();
@@ -1272,8 +1324,12 @@ __global__ __launch_bounds__(64) void k_push_scatter(KParams kp, int C, const in
   extern __shared__ __attribute__((aligned(32))) unsigned char smem[];
   const int lane = threadIdx.x;
   const PC<T> pc(kp);
-  const Segment<T, DIM> sg =
-      stage_segment<T, DIM>(kp, C, xcd_remap(blockIdx.x, gridDim.x), pc, bin_start, Es, Bs, smem, lane);
+  const int wave = segment_wave(kp, C, blockIdx.x, gridDim.x);
+  const Segment<T, DIM> sg = stage_segment<T, DIM>(kp, C, wave, pc, bin_start, Es, Bs, smem, lane);
+  if (sg.C == 0) {
+    if (lane == 0) kep[wave] = 0.0;
+    return;
+  }
   const int S = kp.nspecies;
   const size_t nbins = (size_t)kp.nbins;
   // one lane per bin of the segment, all moves at once: the 2 NDIR loads
@@ -1352,7 +1408,7 @@ __global__ __launch_bounds__(64) void k_push_scatter(KParams kp, int C, const in
   // with the same value), one partial per segment
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) ke += __shfl_xor(ke, o);
-  if (lane == 0) kep[xcd_remap(blockIdx.x, gridDim.x)] = ke;
+  if (lane == 0) kep[wave] = ke;
 }
 
 // ---------------------------------------------------------------------------
@@ -1507,7 +1563,7 @@ void deposit3_impl(const KParams &kp, const PartPtrs &pp, const void *Bst, void 
 template <typename T, int DIM, bool COUNT, int GB>
 void push_launch(const KParams &kp, int C, const PartPtrs &pp, const void *Est, const void *Bst, uint8_t *dirc,
                  uint16_t *cnt, int32_t *err, void *sink, void *gnx, unsigned long long *chg, hipStream_t st) {
-  const int nblk = kp.ncells / C;
+  const int nblk = segment_waves(kp, C);
   const size_t lds = segment_lds_bytes<T, DIM>(C, kp.nspecies);
   hipLaunchKernelGGL((k_push<T, DIM, COUNT, GB>), dim3(nblk), dim3(64), lds, st, kp, C, pp.bin_start,
                      mp<V2<T>>(pp.xy), mp<V4<T>>(pp.uw), mp<T>(pp.z), cp<V4<T>>(Est), cp<V4<T>>(Bst), dirc, cnt, err,
@@ -1544,7 +1600,7 @@ void scatter_launch(const KParams &kp, int C, const PartPtrs &src, const void *E
                     const uint8_t *dirc, const uint16_t *pre, const int32_t *bsn, const PartPtrs &out, int ntot,
                     int32_t *err, unsigned long long *clamps, int32_t *perm, void *sink, double *kep,
                     hipStream_t st) {
-  const int nblk = kp.ncells / C;
+  const int nblk = segment_waves(kp, C);
   const size_t lds = segment_lds_bytes<T, DIM>(C, kp.nspecies);
   hipLaunchKernelGGL((k_push_scatter<T, DIM, PERM, GB>), dim3(nblk), dim3(64), lds, st, kp, C, src.bin_start,
                      cp<V2<T>>(src.xy), cp<V4<T>>(src.uw), cp<T>(src.z), cp<V4<T>>(Est), cp<V4<T>>(Bst), dirc, pre,
@@ -1652,6 +1708,8 @@ void launch_assemble(const KParams &kp, int prec, int mass_fp32, const void *S, 
   else
     assemble_as<float, double>(kp, S, J, M, st);
 }
+
+int push_waves(const KParams &kp, int cells) { return segment_waves(kp, cells); }
 
 size_t push_lds_bytes(const KParams &kp, int prec, int cells) {
   const bool f = prec == RELSIM_MIXED;

@@ -15,7 +15,7 @@ namespace relsim {
 struct KParams {
   int dim, nx, ny, nz, ncells, nspecies, nbins, nonrel;
   int tx, ty, tz;     // tile extents of the particle kernels' cell order (powers of two dividing nx, ny, nz)
-  int sty, stz;       // y and z extents of the push passes' segment tiles (powers of two dividing ny, nz)
+  int sty, stz;       // y and z extents of the push passes' segment tiles (the last ones may reach past the grid)
   int ltx, lty, ltz;  // their base-2 logarithms
   int ntx, nty;       // tiles along x and y
   int gx, gxy;        // strides of the ghosted field copies: nx + 2, (nx + 2)(ny + 2)
@@ -44,6 +44,14 @@ constexpr int kSinkSlots = 512;     // per-lane store sinks of the particle kern
 // Moments per cell: 2D 81 mass moments + 12 current moments; 3D 3 x 81 mass
 // moments (one set per z-monomial type) plus 2 x 12 current moments.
 inline int n_cell_moments(int dim) { return dim == 3 ? 3 * 81 + 2 * 12 : 81 + 12; }
+
+// Extent of equal tiles of about `cap` that cover n places: n / cap rounded
+// down or up tiles, whichever reaches less far past n.
+__host__ __device__ inline int even_tile(int n, int cap) {
+  const int hi = (n + cap - 1) / cap, lo = n / cap > 0 ? n / cap : 1;
+  const int eh = (n + hi - 1) / hi, el = (n + lo - 1) / lo;
+  return el * lo < eh * hi ? el : eh;
+}
 
 // Per-cell moments in memory (93 per cell in 2D, 267 in 3D): blocks of 64
 // consecutive cells, each block holding its moments as 64-cell rows, moment
@@ -129,10 +137,12 @@ void launch_assemble(const KParams &kp, int prec, int mass_fp32, const void *S, 
                      hipStream_t st);
 // `sink`: kSinkSlots * 64 * 32 bytes of workspace that lanes without a
 // particle store into (contents meaningless)
-// The push passes give each wave `cells` consecutive cells of one grid row
-// (a power of two dividing nx); push_lds_bytes is the LDS one wave stages.
+// The push passes give each wave `cells` (a power of two) consecutive cells
+// of one grid row, the last segment of a row possibly fewer; push_waves is
+// the number of waves and push_lds_bytes the LDS one of them stages.
 // count_moves: only read the particles and write each one's move (dirc) and
 // the per-(move, bin) counts (first pass of the re-sort); else push in place
+int push_waves(const KParams &kp, int cells);
 size_t push_lds_bytes(const KParams &kp, int prec, int cells);
 void launch_push(const KParams &kp, int prec, int cells, const PartPtrs &pp, const void *Est, const void *Bst,
                  uint8_t *dirc, uint16_t *cnt, int32_t *err, int count_moves, void *sink, hipStream_t st);
@@ -153,8 +163,8 @@ size_t scan_tmp_elems(int n);
 // out in the new bin order, each in the cell of its recorded move (err bit
 // 8: a recomputed position further than rounding outside that cell; *clamps
 // += particles within rounding outside it, put on its face).  kep[w] gets
-// the FP64 kinetic energy of the particles wave w pushed (ncells / cells
-// waves; w in the segment order).
+// the FP64 kinetic energy of the particles wave w pushed (push_waves of them,
+// in the segment order).
 void launch_push_scatter(const KParams &kp, int prec, int cells, const PartPtrs &src, const void *Est,
                          const void *Bst, const uint8_t *dirc, const uint16_t *pre, const int32_t *bin_start_new,
                          const PartPtrs &out, int ntot, int32_t *err, unsigned long long *clamps, int32_t *perm,
