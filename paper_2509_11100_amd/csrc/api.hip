@@ -888,10 +888,8 @@ int relsim_apply_AT(relsim_ctx *c, const void *M, const double *x, double *out) 
 static AdjInPtrs adj_inputs(const relsim_particles *pt) {
   AdjInPtrs a;
   a.bin_start = pt->bin_start;
-  a.cell = pt->cell;
   a.xy = (const double *)pt->xy;
   a.uw = (const double *)pt->uw;
-  a.z = (const double *)pt->z;
   return a;
 }
 
@@ -907,7 +905,7 @@ int relsim_push_adjoint(relsim_ctx *c, const relsim_particles *state_n, const do
     return fail(c, RELSIM_EINVAL, "null argument");
   timed(c, "push_adjoint", [&] {
     launch_push_adjoint(c->kp, adj_inputs(state_n), (int)state_n->n, E_theta, B_n, new_index, lam_x_in, lam_u_in,
-                        lam_x_out, lam_u_out, lam_E_theta, lam_B_n, c->st);
+                        lam_x_out, lam_u_out, lam_E_theta, lam_B_n, c->at<double>(c->L.S), c->st);
   });
   return launch_status(c, "relsim_push_adjoint");
 }
@@ -937,7 +935,7 @@ int relsim_deposit_adjoint(relsim_ctx *c, const relsim_particles *state_n, const
     return fail(c, RELSIM_EINVAL, "null argument");
   timed(c, "deposit_adjoint", [&] {
     launch_deposit_adjoint(c->kp, adj_inputs(state_n), (int)state_n->n, B_n, E_theta, mu, lam_x, lam_u, lam_B_n,
-                           c->st);
+                           c->at<double>(c->L.S), c->st);
   });
   return launch_status(c, "relsim_deposit_adjoint");
 }

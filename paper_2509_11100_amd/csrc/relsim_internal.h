@@ -183,16 +183,15 @@ void launch_gsort(const KParams &kp, int prec, int64_t n, const int32_t *cell, c
 // ---- adjoint kernels (adjoint.hip), FP64 particle state ----
 struct AdjInPtrs {
   const int32_t *bin_start = nullptr;
-  const int32_t *cell = nullptr;
   const double *xy = nullptr;  // 2D: [n] (off_x, off_y); 3D: [n] 8-value records
   const double *uw = nullptr;  // 2D: [n] (u_x, u_y, u_z, w); unused in 3D
-  const double *z = nullptr;   // unused
 };
+// sums: scratch, (3 2^dim + 3^{dim+1}) ncells doubles
 void launch_push_adjoint(const KParams &kp, const AdjInPtrs &in, int n, const double *Eth, const double *B,
                          const int32_t *new_index, const double *lx_in, const double *lu_in, double *lx_out,
-                         double *lu_out, double *lEth, double *lB, hipStream_t st);
+                         double *lu_out, double *lEth, double *lB, double *sums, hipStream_t st);
 void launch_deposit_adjoint(const KParams &kp, const AdjInPtrs &in, int n, const double *B, const double *Eth,
-                            const double *mu, double *lx_out, double *lu_out, double *lB, hipStream_t st);
+                            const double *mu, double *lx_out, double *lu_out, double *lB, double *sums, hipStream_t st);
 
 // ---- field kernels (field.hip) ----
 void launch_curl(const KParams &kp, const double *in, double *out, int to_centres, hipStream_t st);
