@@ -153,6 +153,8 @@ int validate(const relsim_params *p, std::string &msg) {
   return RELSIM_OK;
 }
 
+constexpr int kMostBlocks = std::max(kGmNodeBlocks, kGmTileBlocks);
+
 // Stride of the Krylov basis's rows: even, for 16-byte access.
 size_t gm_stride(size_t n3) { return (n3 + 1) & ~(size_t)1; }
 
@@ -206,10 +208,9 @@ Layout make_layout(const relsim_params *p) {
   L.dirc = take(np);
   L.err = take(64);
   L.gm_V = take((size_t)(p->gmres_restart + 1) * gm_stride(n3) * 8);
-  L.gm_t = take(n3 * 8);
   L.gm_b = take(n3 * 8);
   L.gm_r = take(gm_stride(n3) * 8);
-  L.gm_part = take(((size_t)kGmNodeBlocks * (2 * kMaxRestart + 3) + kGmVecBlocks) * 8);
+  L.gm_part = take(((size_t)kMostBlocks * (2 * kMaxRestart + 3) + kGmVecBlocks) * 8);
   L.gm_state = take(sizeof(GmState));
   L.red_res = take(8 * 8);
   L.red_part = take((size_t)kRedBlocks * 8 * 4);
@@ -301,6 +302,7 @@ KParams make_kparams(const relsim_params *p) {
   k.f_inv_dx = (float)k.inv_dx;
   k.f_inv_dy = (float)k.inv_dy;
   k.f_inv_dz = (float)k.inv_dz;
+  if (p->dim == 3) plan_tiles3(k);
   return k;
 }
 
@@ -460,12 +462,10 @@ int fetch(relsim_ctx *c, const double *dev, int k) {
   return RELSIM_OK;
 }
 
-// out = A x or A^T x (gm_t is the 3D curl's scratch)
+// out = A x or A^T x
 void apply_A(relsim_ctx *c, bool transpose, const void *M, const double *x, double *out) {
-  double *t = c->at<double>(c->L.gm_t);
-  if (c->kp.dim == 3) timed(c, "curl_nc", [&] { launch_curl(c->kp, x, t, 1, c->st); });
   timed(c, transpose ? "apply_AT" : "apply_A",
-        [&] { launch_apply(c->kp, c->p.mass_fp32, transpose, M, x, t, out, c->st); });
+        [&] { launch_apply(c->kp, c->p.mass_fp32, transpose, M, x, out, c->st); });
 }
 
 }  // namespace
@@ -789,12 +789,11 @@ static int gmres_solve(relsim_ctx *c, const void *M, bool transpose, double *x, 
   gm.n3 = 3 * (size_t)c->kp.ncells;
   gm.ld = gm_stride(gm.n3);
   gm.V = c->at<double>(c->L.gm_V);
-  gm.t = c->at<double>(c->L.gm_t);
   gm.b = c->at<double>(c->L.gm_b);
   gm.r = c->at<double>(c->L.gm_r);
   gm.p1 = c->at<double>(c->L.gm_part);
-  gm.p3 = gm.p1 + (size_t)kGmNodeBlocks * (2 * kMaxRestart + 1);
-  gm.p2 = gm.p3 + 2 * kGmNodeBlocks;
+  gm.p3 = gm.p1 + (size_t)kMostBlocks * (2 * kMaxRestart + 1);
+  gm.p2 = gm.p3 + 2 * kMostBlocks;
   gm.st = c->at<GmState>(c->L.gm_state);
   gm.m = c->p.gmres_restart;
   gm.maxit = c->p.gmres_maxit;

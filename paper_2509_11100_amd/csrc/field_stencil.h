@@ -1,5 +1,5 @@
 // Stencils of the implicit field solve, shared by the field kernels and the
-// GMRES kernels: the curl of a cube of values and the mass-matrix product.
+// GMRES kernels: the curl of a cube of values.
 //
 // Both curls use one stencil shape: the difference along d averaged over the
 // transverse corners of a 2x2(x2) cube.  Nodes -> centre of cell (i,j,k)
@@ -61,50 +61,6 @@ __device__ __forceinline__ void cube_curl(const KParams &kp, const double c[3][8
   out[0] = d[2][1] - d[1][2];
   out[1] = d[0][2] - d[2][0];
   out[2] = d[1][0] - d[0][1];
-}
-
-// Linear index of node (i + dx, j + dy, k + dz), periodic.
-template <int DIM>
-__device__ __forceinline__ size_t node_at(const KParams &kp, int i, int j, int k, int dx, int dy, int dz) {
-  return (size_t)wrapi(i + dx, kp.nx) +
-         (size_t)kp.nx * ((size_t)wrapi(j + dy, kp.ny) + (size_t)kp.ny * (DIM == 3 ? wrapi(k + dz, kp.nz) : 0));
-}
-
-// (M x)_g, or (M^T x)_g with TR (each 3x3 block transposed), from the stored
-// half of the blocks: slot h of node g couples x at g + delta(h), and for
-// h > 0 the same slot of node g - delta(h) couples x at g - delta(h)
-// (M_{g,g-delta} = M_{g-delta,g}).  MT is M's storage type (double, or
-// float on request in mixed precision); the products and sums are FP64.
-template <int DIM, bool TR, typename MT>
-__device__ __forceinline__ void apply_M(const KParams &kp, const MT *__restrict__ M,
-                                        const double *__restrict__ x, int g, int i, int j, int k, double mx[3]) {
-  constexpr int NSLOT = m_slots<DIM>(), CEN = m_centre<DIM>();
-  const size_t N = (size_t)kp.ncells;
-#pragma unroll
-  for (int h = 0; h < NSLOT; ++h) {
-    const int off = CEN + h;
-    const int dx = off % 3 - 1, dy = (off / 3) % 3 - 1, dz = DIM == 3 ? off / 9 - 1 : 0;
-#pragma unroll
-    for (int side = 0; side < (h ? 2 : 1); ++side) {
-      // side 0: own block times x at g + delta; side 1: the neighbour's
-      // block times x at g - delta
-      const size_t id = side ? node_at<DIM>(kp, i, j, k, -dx, -dy, -dz) : node_at<DIM>(kp, i, j, k, dx, dy, dz);
-      const double x0 = x[id], x1 = x[N + id], x2 = x[2 * N + id];
-      const MT *Mo = M + (size_t)h * 9 * N + (side ? id : (size_t)g);
-      double m[9];
-#pragma unroll
-      for (int q = 0; q < 9; ++q) m[q] = (double)Mo[q * N];
-      if constexpr (!TR) {
-        mx[0] += m[0] * x0 + m[1] * x1 + m[2] * x2;
-        mx[1] += m[3] * x0 + m[4] * x1 + m[5] * x2;
-        mx[2] += m[6] * x0 + m[7] * x1 + m[8] * x2;
-      } else {
-        mx[0] += m[0] * x0 + m[3] * x1 + m[6] * x2;
-        mx[1] += m[1] * x0 + m[4] * x1 + m[7] * x2;
-        mx[2] += m[2] * x0 + m[5] * x1 + m[8] * x2;
-      }
-    }
-  }
 }
 
 }  // namespace

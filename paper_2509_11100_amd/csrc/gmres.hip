@@ -30,6 +30,7 @@
 // are taken in a fixed order (per thread, wave, block, then block by block),
 // so a solve is deterministic.
 #include <climits>
+#include <cmath>
 
 #include "field_stencil.h"
 
@@ -43,7 +44,6 @@ constexpr int NW = TB / 64;
 // Each XCD (blocks are dispatched to the 8 XCDs round robin) works through
 // one contiguous band of the grid, its blocks side by side: a node reads the
 // mass-matrix blocks of the rows below it, which are then in the same L2.
-// gridDim.x is the number of groups, or kGmNodeBlocks (a multiple of 8).
 struct Groups {
   int first, last, step;
 };
@@ -53,6 +53,7 @@ __device__ __forceinline__ Groups block_groups(int ng) {
     const int first = xcd_remap(b, nb);
     return {first, first + 1, 1};
   }
+  if (nb & 7) return {b, ng, nb};
   const int band = (ng + 7) >> 3, x = b & 7;
   const int lo = x * band;
   return {lo + (b >> 3), lo + band < ng ? lo + band : ng, nb >> 3};
@@ -77,7 +78,7 @@ __host__ __device__ inline int node_groups(const KParams &kp) {
 }
 
 // Sum of acc[q] (q < nv) over the block into P[q * gridDim.x + block].
-template <int NV>
+template <int NV, int NW = kGmThreads / 64>
 __device__ __forceinline__ void put_partials(const double (&acc)[NV], int nv, double *lds, double *__restrict__ P) {
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
 #pragma unroll
@@ -90,7 +91,7 @@ __device__ __forceinline__ void put_partials(const double (&acc)[NV], int nv, do
     }
   }
   __syncthreads();
-  for (int q = threadIdx.x; q < nv; q += TB) {
+  for (int q = threadIdx.x; q < nv; q += 64 * NW) {
     double s = lds[q];
 #pragma unroll
     for (int w = 1; w < NW; ++w) s += lds[w * NV + q];
@@ -100,6 +101,7 @@ __device__ __forceinline__ void put_partials(const double (&acc)[NV], int nv, do
 
 // out[q] (LDS) = the sum over the blocks of partials P[q][.], q < nv; every
 // block forms the same sums.  Ends with a barrier.
+template <int NW = kGmThreads / 64>
 __device__ __forceinline__ void get_sums(const double *__restrict__ P, int nparts, int nv, double *out) {
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   for (int q = wid; q < nv; q += NW) {
@@ -116,7 +118,9 @@ __device__ __forceinline__ void get_sums(const double *__restrict__ P, int npart
 
 // Whether the kernels of column j have nothing to do: the solve has ended,
 // or its cycle ended with an earlier column.  A block that starts after block
-// 0 of its own kernel has recorded an end would come to the same end.
+// 0 of its own kernel has recorded an end would come to the same end.  One
+// thread of a block reads the state for all of it, so that the block stays
+// together.
 __device__ __forceinline__ bool arnoldi_off(const GmState *st, int j) {
   return st->code != 0 || st->done != 0 || (st->end_at >= 0 && st->end_at < j);
 }
@@ -125,18 +129,36 @@ __device__ __forceinline__ bool tail_off(const GmState *st) {
   return st->code != 0 || st->done != 0 || st->end_at < 0;
 }
 
-// (A x)_g or (A^T x)_g.  In 2D the 3 x 3 nodes around g hold all that the
-// curl of the curl and the mass matrix read, and the curl is formed again for
-// each of the 4 cells around g; in 3D t = C_NC x is given.
-template <int DIM, bool TR, typename MT>
+// Adds the 3x3 block m, or its transpose, times x to y.
+template <bool TR>
+__device__ __forceinline__ void add_block(const double m[9], const double x[3], double y[3]) {
+  if constexpr (!TR) {
+    y[0] += m[0] * x[0] + m[1] * x[1] + m[2] * x[2];
+    y[1] += m[3] * x[0] + m[4] * x[1] + m[5] * x[2];
+    y[2] += m[6] * x[0] + m[7] * x[1] + m[8] * x[2];
+  } else {
+    y[0] += m[0] * x[0] + m[3] * x[1] + m[6] * x[2];
+    y[1] += m[1] * x[0] + m[4] * x[1] + m[7] * x[2];
+    y[2] += m[2] * x[0] + m[5] * x[1] + m[8] * x[2];
+  }
+}
+template <typename MT>
+__device__ __forceinline__ void load_block(const MT *__restrict__ M, size_t N, double m[9]) {
+#pragma unroll
+  for (int e = 0; e < 9; ++e) m[e] = (double)M[e * N];
+}
+
+// (A x)_g or (A^T x)_g in 2D: the 3 x 3 nodes around g hold all that the curl
+// of the curl and the mass matrix read, and the curl is formed again for each
+// of the 4 cells around g.
+template <bool TR, typename MT>
 __device__ __forceinline__ void apply_node(const KParams &kp, const MT *__restrict__ M, const double *__restrict__ x,
-                                           const double *__restrict__ t, int g, int i, int j, int k, double xc[3],
-                                           double out[3]) {
+                                           int g, int i, int j, double xc[3], double out[3]) {
   const size_t N = (size_t)kp.ncells;
   const double a = kp.c * kp.theta * kp.dt;
   const double b = 4.0 * M_PI * kp.theta * kp.dt;
   double mx[3] = {0.0, 0.0, 0.0}, cc[3];
-  if constexpr (DIM == 2) {
+  {
     int id[9];
     double x9[3][9];
     const int im = wrapi(i - 1, kp.nx), ip = wrapi(i + 1, kp.nx);
@@ -157,18 +179,9 @@ __device__ __forceinline__ void apply_node(const KParams &kp, const MT *__restri
         const int q = side ? 4 - h : 4 + h;
         const MT *Mo = M + (size_t)h * 9 * N + (side ? id[q] : g);
         double m[9];
-#pragma unroll
-        for (int e = 0; e < 9; ++e) m[e] = (double)Mo[e * N];
-        const double x0 = x9[0][q], x1 = x9[1][q], x2 = x9[2][q];
-        if constexpr (!TR) {
-          mx[0] += m[0] * x0 + m[1] * x1 + m[2] * x2;
-          mx[1] += m[3] * x0 + m[4] * x1 + m[5] * x2;
-          mx[2] += m[6] * x0 + m[7] * x1 + m[8] * x2;
-        } else {
-          mx[0] += m[0] * x0 + m[3] * x1 + m[6] * x2;
-          mx[1] += m[1] * x0 + m[4] * x1 + m[7] * x2;
-          mx[2] += m[2] * x0 + m[5] * x1 + m[8] * x2;
-        }
+        load_block<MT>(Mo, N, m);
+        const double xq[3] = {x9[0][q], x9[1][q], x9[2][q]};
+        add_block<TR>(m, xq, mx);
       }
     }
     double tc[3][8];
@@ -188,51 +201,317 @@ __device__ __forceinline__ void apply_node(const KParams &kp, const MT *__restri
     cube_curl<2>(kp, tc, cc);
 #pragma unroll
     for (int c = 0; c < 3; ++c) xc[c] = x9[c][4];
-  } else {
-    double c[3][8];
-    load_cube<3>(kp, t, i - 1, j - 1, k - 1, c);
-    cube_curl<3>(kp, c, cc);
-    apply_M<3, TR, MT>(kp, M, x, g, i, j, k, mx);
-#pragma unroll
-    for (int q = 0; q < 3; ++q) xc[q] = x[q * N + g];
   }
 #pragma unroll
   for (int q = 0; q < 3; ++q) out[q] = xc[q] + a * a * cc[q] + b * mx[q];
 }
 
-// out = A x or A^T x (relsim_apply_A, relsim_apply_AT)
-template <int DIM, bool TR, typename MT>
-__global__ __launch_bounds__(TB) void k_apply(KParams kp, const MT *__restrict__ M, const double *__restrict__ x,
-                                              const double *__restrict__ t, double *__restrict__ out) {
-  const size_t N = (size_t)kp.ncells;
-  const Groups gr = block_groups(node_groups(kp));
-  for (int grp = gr.first; grp < gr.last; grp += gr.step) {
-    int i, j, k;
-    const int g = group_node<DIM>(kp, grp, i, j, k);
-    if (g < 0) continue;
-    double xc[3], y[3];
-    apply_node<DIM, TR, MT>(kp, M, x, t, g, i, j, k, xc, y);
+
+// ---------------------------------------------------------------------------
+// The operator in 3D: a march over z with every stored block read once.
+//
+// A node's 14 blocks couple it to 13 nodes ahead of it, and 13 nodes behind it
+// hold the blocks that couple it to them.  Gathering those again from memory
+// made the operator read 1.5 times the stored blocks (6.5 GB on the 256 x 128
+// x 128 grid, 1.35 ms and 0.08 ms for the curl, at the memory's rate).  Here a
+// block of waves owns a tile of w x ty nodes and marches over lz planes: lane
+// and wave are a node's x and y, and a block read once gives both products, M
+// x_{g+d} for its own node and M x_g for node g + d.  The latter goes to its
+// lane by a lane shift, to its row through LDS and to the next plane in
+// registers.  Nodes around the tile whose blocks reach into it are done again
+// by the tile: a lane on either side of the row, a wave before (6 of 14
+// blocks) and a wave behind (3) and the plane before the first (9).  The curl
+// of the curl comes along: t = C_NC x of the wave's cells, shifted and passed
+// the same way.  Counted 5.5 GB, 1.18 ms (4.7 TB/s); tiles of 2, 6, 8, 10 and
+// 14 rows took 14.9, 14.2, 14.3, 14.3 and 15.2 ms for the whole solve (the
+// last ones spill), and loading the next plane's first blocks ahead of the
+// exchange 14.2.  The blocks are loaded a row (of three) ahead of their use:
+// on smaller grids, where the caches hold part of M, a wave's loads in flight
+// count (128 x 64 x 64, M in FP32: 1.84 -> 1.45 ms; gathering, 1.66 ms).
+// ---------------------------------------------------------------------------
+constexpr int kRows3 = 6;             // most rows of a tile
+constexpr int NW3 = kRows3 + 2;       // waves: the rows and one on either side
+constexpr int TB3 = 64 * NW3;
+
+// Tiles of w x ty x lz nodes (plan_tiles3), the last ones along y and z
+// possibly smaller.
+struct Tiles3 {
+  int w, ty, lz, ntx, nty, ntz;
+  __host__ __device__ explicit Tiles3(const KParams &kp) : w(kp.t3x), ty(kp.t3y), lz(kp.t3z) {
+    ntx = (kp.nx + w - 1) / w;
+    nty = (kp.ny + ty - 1) / ty;
+    ntz = (kp.nz + lz - 1) / lz;
+  }
+  __host__ __device__ int count() const { return ntx * nty * ntz; }
+};
+
+struct D3 {
+  double x, y, z;
+};
+struct Planes3 {
+  D3 a[NW3][64], b[NW3][64], c[NW3][64], t[NW3][64];
+};
+
+__device__ __forceinline__ D3 d3(const double v[3]) { return D3{v[0], v[1], v[2]}; }
+
+// v of the lane to the left (x - 1) or right (x + 1)
+template <bool RIGHT>
+__device__ __forceinline__ double beside(double v) {
+  constexpr int ctrl = RIGHT ? 0x130 : 0x138;  // DPP wave_shl:1, wave_shr:1
+  const long long b = __double_as_longlong(v);
+  const int lo = __builtin_amdgcn_update_dpp(0, (int)b, ctrl, 0xf, 0xf, true);
+  const int hi = __builtin_amdgcn_update_dpp(0, (int)(b >> 32), ctrl, 0xf, 0xf, true);
+  return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
+}
+// x of the node at dx, seen from this lane
+template <int DX>
+__device__ __forceinline__ void at_dx(const double v[3], double out[3]) {
 #pragma unroll
-    for (int c = 0; c < 3; ++c) out[c * N + g] = y[c];
+  for (int q = 0; q < 3; ++q) out[q] = DX == 0 ? v[q] : (DX > 0 ? beside<true>(v[q]) : beside<false>(v[q]));
+}
+// sum += c moved to the lane at dx
+template <int DX>
+__device__ __forceinline__ void send_dx(const double c[3], double sum[3]) {
+#pragma unroll
+  for (int q = 0; q < 3; ++q) sum[q] += DX == 0 ? c[q] : (DX > 0 ? beside<false>(c[q]) : beside<true>(c[q]));
+}
+
+// Block m at DX of the lane's node (x = x_g): with GATHER its product with the
+// x at DX (of the row and plane given, xr) is added to y, with SEND its
+// product with x_g to sum at DX.
+template <bool TR, int DX, bool GATHER, bool SEND>
+__device__ __forceinline__ void use_block(const double m[9], const double x[3], const double xr[3], double y[3],
+                                          double sum[3]) {
+  if constexpr (GATHER) {
+    double v[3];
+    at_dx<DX>(xr, v);
+    add_block<TR>(m, v, y);
+  }
+  if constexpr (SEND) {
+    double c[3] = {0.0, 0.0, 0.0};
+    add_block<TR>(m, x, c);
+    send_dx<DX>(c, sum);
+  }
+}
+// NB consecutive blocks from slot h on, loaded; three of them, at dx = -1, 0, 1
+// of one row, used
+template <int NB, typename MT>
+__device__ __forceinline__ void load_row(const MT *__restrict__ M, size_t N, int h, int g, MT m[27]) {
+#pragma unroll
+  for (int e = 0; e < 9 * NB; ++e) m[e] = M[((size_t)h * 9 + e) * N + g];
+}
+template <typename MT>
+__device__ __forceinline__ void as_double(const MT *m, double d[9]) {
+#pragma unroll
+  for (int e = 0; e < 9; ++e) d[e] = (double)m[e];
+}
+template <bool TR, bool GATHER, bool SEND, typename MT>
+__device__ __forceinline__ void use_row(const MT m[27], const double x[3], const double xr[3], double y[3],
+                                        double sum[3]) {
+  double d[9];
+  as_double(m, d);
+  use_block<TR, -1, GATHER, SEND>(d, x, xr, y, sum);
+  as_double(m + 9, d);
+  use_block<TR, 0, GATHER, SEND>(d, x, xr, y, sum);
+  as_double(m + 18, d);
+  use_block<TR, 1, GATHER, SEND>(d, x, xr, y, sum);
+}
+
+// Barrier for the LDS exchange only: loads of the next planes stay in flight.
+__device__ __forceinline__ void lds_barrier() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+  __builtin_amdgcn_s_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+}
+
+// Calls out(g, x_g, (A x)_g) for every node of the block's tiles, in the
+// lanes and waves that own them, and before that pre(g), before the loads of
+// the node's plane (also for the lanes beside).
+template <bool TR, typename MT, typename P, typename F>
+__device__ __forceinline__ void march3(const KParams &kp, const MT *__restrict__ M, const double *__restrict__ x,
+                                       Planes3 &sh, P &&pre, F &&out) {
+  const size_t N = (size_t)kp.ncells;
+  const int lane = threadIdx.x & 63, rw = threadIdx.x >> 6;
+  const Tiles3 tl(kp);
+  const double a = kp.c * kp.theta * kp.dt;
+  const double b = 4.0 * M_PI * kp.theta * kp.dt;
+  const Groups gr = block_groups(tl.count());
+  for (int tile = gr.first; tile < gr.last; tile += gr.step) {
+    const int t1 = tile / tl.ntx, t2 = t1 / tl.nty;
+    const int i0 = (tile - t1 * tl.ntx) * tl.w, j0 = (t1 - t2 * tl.nty) * tl.ty, k0 = t2 * tl.lz;
+    const int w = tl.w < kp.nx - i0 ? tl.w : kp.nx - i0;
+    const int rows = tl.ty < kp.ny - j0 ? tl.ty : kp.ny - j0;
+    const int planes = tl.lz < kp.nz - k0 ? tl.lz : kp.nz - k0;
+    // lanes past the right neighbour repeat it (their products reach no owned lane)
+    const int i = wrapi(i0 - 1 + (lane < w + 1 ? lane : w + 1), kp.nx);
+    const bool before = rw == 0, own = rw >= 1 && rw <= rows, behind = rw == rows + 1;
+    const bool active = rw <= rows + 1;
+    const int j = active ? wrapi(j0 - 1 + rw, kp.ny) : 0;
+    const int row = i + kp.nx * j, up = i + kp.nx * wrapi(j + 1, kp.ny), down = i + kp.nx * wrapi(j - 1, kp.ny);
+    const int nxy = kp.nx * kp.ny;
+    int k = wrapi(k0 - 1, kp.nz);
+    double x0[3], xp[3], carry[3] = {0, 0, 0}, t0[3] = {0, 0, 0}, tm0[3] = {0, 0, 0};
+    auto load = [&](int plane, int at, double v[3]) {
+      const size_t id = (size_t)plane * nxy + at;
+#pragma unroll
+      for (int q = 0; q < 3; ++q) v[q] = x[q * N + id];
+    };
+    load(k, row, x0);
+    load(k, up, xp);
+    for (int s = -1; s < planes; ++s) {
+      const int kn = k + 1 == kp.nz ? 0 : k + 1;
+      const int g = k * nxy + row;
+      double nm[3], n0[3], np[3], y[3], s0[3], sA[3], sB[3], sC[3], t[3];
+      load(kn, down, nm);
+      load(kn, row, n0);
+      load(kn, up, np);
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+        y[q] = carry[q];
+        s0[q] = sA[q] = sB[q] = sC[q] = 0.0;
+      }
+      // rows of blocks in two buffers, one loaded while the other is used
+      MT ma[27], mb[27];
+      if (own) {
+        if (s >= 0) {
+          double d[9];
+          pre(g);
+          load_row<2>(M, N, 0, g, ma);
+          load_row<3>(M, N, 2, g, mb);
+          as_double(ma, d);
+          add_block<TR>(d, x0, y);
+          as_double(ma + 9, d);
+          use_block<TR, 1, true, true>(d, x0, x0, y, y);
+          load_row<3>(M, N, 5, g, ma);
+          use_row<TR, true, true>(mb, x0, xp, y, sA);
+          load_row<3>(M, N, 8, g, mb);
+          use_row<TR, true, true>(ma, x0, nm, y, sB);
+          load_row<3>(M, N, 11, g, ma);
+          use_row<TR, true, true>(mb, x0, n0, y, s0);
+          use_row<TR, true, true>(ma, x0, np, y, sC);
+        } else {
+          load_row<3>(M, N, 5, g, ma);
+          load_row<3>(M, N, 8, g, mb);
+          use_row<TR, false, true>(ma, x0, nm, y, sB);
+          load_row<3>(M, N, 11, g, ma);
+          use_row<TR, false, true>(mb, x0, n0, y, s0);
+          use_row<TR, false, true>(ma, x0, np, y, sC);
+        }
+      } else if (before) {
+        load_row<3>(M, N, 11, g, ma);
+        if (s >= 0) {
+          load_row<3>(M, N, 2, g, mb);
+          use_row<TR, false, true>(mb, x0, xp, y, sA);
+        }
+        use_row<TR, false, true>(ma, x0, np, y, sC);
+      } else if (behind) {
+        load_row<3>(M, N, 5, g, ma);
+        use_row<TR, false, true>(ma, x0, nm, y, sB);
+      }
+      if (own || before) {
+        double c[3][8];
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+          const double v[4] = {x0[q], xp[q], n0[q], np[q]};
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            c[q][2 * r] = v[r];
+            c[q][2 * r + 1] = beside<true>(v[r]);
+          }
+        }
+        cube_curl<3>(kp, c, t);
+        sh.a[rw][lane] = d3(sA);
+        sh.c[rw][lane] = d3(sC);
+        sh.t[rw][lane] = d3(t);
+      }
+      if (own || behind) sh.b[rw][lane] = d3(sB);
+      lds_barrier();
+      if (own) {
+        const D3 va = sh.a[rw - 1][lane], vc = sh.c[rw - 1][lane], vb = sh.b[rw + 1][lane], vt = sh.t[rw - 1][lane];
+        y[0] += va.x, y[1] += va.y, y[2] += va.z;
+        carry[0] = s0[0] + vc.x + vb.x;
+        carry[1] = s0[1] + vc.y + vb.y;
+        carry[2] = s0[2] + vc.z + vb.z;
+        const double tm[3] = {vt.x, vt.y, vt.z};
+        double c[3][8], cc[3];
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+          const double v[4] = {tm0[q], t0[q], tm[q], t[q]};
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            c[q][2 * r] = beside<false>(v[r]);
+            c[q][2 * r + 1] = v[r];
+          }
+        }
+        cube_curl<3>(kp, c, cc);
+        if (s >= 0 && lane >= 1 && lane <= w) {
+          double r[3];
+#pragma unroll
+          for (int q = 0; q < 3; ++q) r[q] = x0[q] + a * a * cc[q] + b * y[q];
+          out(g, x0, r);
+        }
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+          t0[q] = t[q];
+          tm0[q] = tm[q];
+        }
+      }
+      lds_barrier();
+#pragma unroll
+      for (int q = 0; q < 3; ++q) {
+        x0[q] = n0[q];
+        xp[q] = np[q];
+      }
+      k = kn;
+    }
   }
 }
 
-// t = C_NC x of a vector of the iteration (3D; j: its column, -1 after a
-// cycle, -2 at the start)
-__global__ __launch_bounds__(TB) void k_gm_curl(KParams kp, GmBuf gm, const double *__restrict__ x, int j) {
-  if (j == -2 ? gm.st->code != 0 : (j < 0 ? tail_off(gm.st) : arnoldi_off(gm.st, j))) return;
-  const size_t N = (size_t)kp.ncells;
-  const Groups gr = block_groups(node_groups(kp));
-  for (int grp = gr.first; grp < gr.last; grp += gr.step) {
-    int i, jj, k;
-    const int g = group_node<3>(kp, grp, i, jj, k);
-    if (g < 0) continue;
-    double c[3][8], r[3];
-    load_cube<3>(kp, x, i, jj, k, c);
-    cube_curl<3>(kp, c, r);
-#pragma unroll
-    for (int q = 0; q < 3; ++q) gm.t[q * N + g] = r[q];
+// Calls pre(g), then out(g, x_g, (A x)_g) for the nodes of the block's share of
+// the grid.
+template <int DIM>
+struct Shared {};
+template <>
+struct Shared<3> {
+  Planes3 p;
+};
+struct NoPre {
+  __device__ void operator()(int) const {}
+};
+template <int DIM, bool TR, typename MT, typename P, typename F>
+__device__ __forceinline__ void apply_all(const KParams &kp, const MT *__restrict__ M, const double *__restrict__ x,
+                                          Shared<DIM> &sh, P &&pre, F &&out) {
+  if constexpr (DIM == 3) {
+    march3<TR, MT>(kp, M, x, sh.p, pre, out);
+  } else {
+    const Groups gr = block_groups(node_groups(kp));
+    for (int grp = gr.first; grp < gr.last; grp += gr.step) {
+      int i, j, k;
+      const int g = group_node<2>(kp, grp, i, j, k);
+      if (g < 0) continue;
+      double xc[3], y[3];
+      pre(g);
+      apply_node<TR, MT>(kp, M, x, g, i, j, xc, y);
+      out(g, xc, y);
+    }
   }
+}
+// Threads and waves of the kernels that apply the operator.
+template <int DIM>
+constexpr int kOpThreads = DIM == 3 ? TB3 : TB;
+template <int DIM>
+constexpr int kOpWaves = DIM == 3 ? NW3 : NW;
+
+// y = A x or A^T x (relsim_apply_A, relsim_apply_AT)
+template <int DIM, bool TR, typename MT>
+__global__ __launch_bounds__(kOpThreads<DIM>, DIM == 3 ? NW3 / 4 : 1) void k_apply(KParams kp, const MT *__restrict__ M,
+                                                           const double *__restrict__ x, double *__restrict__ y) {
+  __shared__ Shared<DIM> sh;
+  const size_t N = (size_t)kp.ncells;
+  apply_all<DIM, TR, MT>(kp, M, x, sh, NoPre(), [&](int g, const double *, const double *r) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) y[c * N + g] = r[c];
+  });
 }
 
 __device__ __forceinline__ void init_state(const GmBuf &gm, int code) {
@@ -342,15 +621,20 @@ constexpr int kQ = 4;
 // is |g| |w| / hypot(a, |w|)).  FIRST (j = 0): w is the residual r, whose norm
 // (and in the solve's first cycle the right-hand side's) is summed here.
 template <int DIM, bool TR, typename MT, int NV, bool FIRST>
-__global__ __launch_bounds__(TB, NV <= 32 ? 2 : 1) void k_gm_apply(KParams kp, GmBuf gm, const MT *__restrict__ M, int j, int cycle0) {
+__global__ __launch_bounds__(kOpThreads<DIM>, DIM == 3 ? NW3 / 4 : (NV <= 32 ? 2 : 1)) void k_gm_apply(
+    KParams kp, GmBuf gm, const MT *__restrict__ M, int j, int cycle0) {
+  constexpr int NW = kOpWaves<DIM>;
   __shared__ double lds[NW * (2 * NV + 1)];
+  __shared__ Shared<DIM> sh;
+  __shared__ bool off;
   GmState *const st = gm.st;
-  if (arnoldi_off(st, j)) return;
+  if (threadIdx.x == 0) off = arnoldi_off(st, j);
   const size_t N = (size_t)kp.ncells;
   const bool head = blockIdx.x == 0 && threadIdx.x == 0;
   double wn;
   if constexpr (FIRST) {
-    get_sums(gm.p3, gm.na, 2, lds);
+    get_sums<NW>(gm.p3, gm.na, 2, lds);
+    if (off) return;
     wn = sqrt(lds[1]);
     const double bnorm = cycle0 ? sqrt(lds[0]) : st->bnorm;
     const double tol = gm.rtol * bnorm;
@@ -369,7 +653,8 @@ __global__ __launch_bounds__(TB, NV <= 32 ? 2 : 1) void k_gm_apply(KParams kp, G
     }
     if (code || conv) return;
   } else {
-    get_sums(gm.p2, gm.no, 1, lds);
+    get_sums<NW>(gm.p2, gm.no, 1, lds);
+    if (off) return;
     wn = sqrt(lds[0]);
     const double den = hypot(st->a, wn);
     const double est = den > 0 ? fabs(st->g[j - 1]) * (wn / den) : 0.0;
@@ -393,17 +678,12 @@ __global__ __launch_bounds__(TB, NV <= 32 ? 2 : 1) void k_gm_apply(KParams kp, G
   double acc[2 * NV + 1];
 #pragma unroll
   for (int q = 0; q <= 2 * NV; ++q) acc[q] = 0.0;
-  const Groups gr = block_groups(node_groups(kp));
-  for (int grp = gr.first; grp < gr.last; grp += gr.step) {
-    int i, jj, k;
-    const int g = group_node<DIM>(kp, grp, i, jj, k);
-    if (g < 0) continue;
+  apply_all<DIM, TR, MT>(kp, M, x, sh, NoPre(), [&](int g, const double *xg, const double *r) {
     double w[3], y[3];
-    apply_node<DIM, TR, MT>(kp, M, x, gm.t, g, i, jj, k, w, y);
 #pragma unroll
     for (int c = 0; c < 3; ++c) {
-      w[c] *= inv;
-      y[c] *= inv;
+      w[c] = inv * xg[c];
+      y[c] = inv * r[c];
       u[c * N + g] = y[c];
       acc[0] += w[c] * y[c];
     }
@@ -424,7 +704,7 @@ __global__ __launch_bounds__(TB, NV <= 32 ? 2 : 1) void k_gm_apply(KParams kp, G
         }
       }
     }
-  }
+  });
   // partial sums: w~.u, s_0 .. s_{j-1}, z_0 .. z_{j-1}
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
 #pragma unroll
@@ -438,7 +718,7 @@ __global__ __launch_bounds__(TB, NV <= 32 ? 2 : 1) void k_gm_apply(KParams kp, G
     }
   }
   __syncthreads();
-  for (int q = threadIdx.x; q <= 2 * j; q += TB) {
+  for (int q = threadIdx.x; q <= 2 * j; q += 64 * NW) {
     double s = lds[q];
 #pragma unroll
     for (int w = 1; w < NW; ++w) s += lds[w * (2 * NV + 1) + q];
@@ -510,9 +790,11 @@ __device__ void hessenberg_column(const GmBuf &gm, int j, const double *s, const
 // before.
 __global__ __launch_bounds__(TB) void k_gm_ortho(GmBuf gm, int j) {
   __shared__ double sums[2 * kMaxRestart + 1], s[kMaxRestart], z[kMaxRestart], hh[2 * (kMaxRestart + 1)], lds[NW];
+  __shared__ bool off;
   GmState *const st = gm.st;
-  if (arnoldi_off(st, j)) return;
+  if (threadIdx.x == 0) off = arnoldi_off(st, j);
   get_sums(gm.p1, gm.na, 2 * j + 1, sums);
+  if (off) return;
   const int jq = (j + kQ - 1) / kQ * kQ;
   for (int q = threadIdx.x; q < jq; q += TB) {
     s[q] = q < j ? sums[1 + q] : 0.0;
@@ -570,8 +852,11 @@ __global__ __launch_bounds__(TB) void k_gm_ortho(GmBuf gm, int j) {
 // time over the lanes of one wave) and x += V y.
 __global__ __launch_bounds__(TB) void k_gm_update(GmBuf gm, double *__restrict__ x) {
   __shared__ double y[kMaxRestart];
+  __shared__ bool off;
   const GmState *const st = gm.st;
-  if (tail_off(st)) return;
+  if (threadIdx.x == 0) off = tail_off(st);
+  __syncthreads();
+  if (off) return;
   const int n = st->end_at + 1;
   if (threadIdx.x < 64) {
     const int lane = threadIdx.x;  // n <= 64: one row per lane
@@ -596,41 +881,43 @@ __global__ __launch_bounds__(TB) void k_gm_update(GmBuf gm, double *__restrict__
 // r = b - A x and the partial sums of r.r (beside those of b.b), at the
 // start or after a cycle
 template <int DIM, bool TR, typename MT>
-__global__ __launch_bounds__(TB) void k_gm_residual(KParams kp, GmBuf gm, const MT *__restrict__ M,
-                                                    const double *__restrict__ x, int start) {
-  __shared__ double lds[NW];
-  if (start ? gm.st->code != 0 : tail_off(gm.st)) return;
+__global__ __launch_bounds__(kOpThreads<DIM>, DIM == 3 ? NW3 / 4 : 1) void k_gm_residual(KParams kp, GmBuf gm, const MT *__restrict__ M,
+                                                                 const double *__restrict__ x, int start) {
+  __shared__ double lds[kOpWaves<DIM>];
+  __shared__ Shared<DIM> sh;
+  __shared__ bool off;
+  if (threadIdx.x == 0) off = start ? gm.st->code != 0 : tail_off(gm.st);
+  __syncthreads();
+  if (off) return;
   const size_t N = (size_t)kp.ncells;
-  double acc[1] = {0.0};
-  const Groups gr = block_groups(node_groups(kp));
-  for (int grp = gr.first; grp < gr.last; grp += gr.step) {
-    int i, j, k;
-    const int g = group_node<DIM>(kp, grp, i, j, k);
-    if (g < 0) continue;
-    double xc[3], y[3];
-    apply_node<DIM, TR, MT>(kp, M, x, gm.t, g, i, j, k, xc, y);
+  double acc[1] = {0.0}, bg[3];
+  auto pre = [&](int g) {
+#pragma unroll
+    for (int q = 0; q < 3; ++q) bg[q] = gm.b[q * N + g];
+  };
+  apply_all<DIM, TR, MT>(kp, M, x, sh, pre, [&](int g, const double *, const double *y) {
 #pragma unroll
     for (int q = 0; q < 3; ++q) {
-      const double rq = gm.b[q * N + g] - y[q];
+      const double rq = bg[q] - y[q];
       gm.r[q * N + g] = rq;
       acc[0] += rq * rq;
     }
-  }
-  put_partials<1>(acc, 1, lds, gm.p3 + gridDim.x);
+  });
+  put_partials<1, kOpWaves<DIM>>(acc, 1, lds, gm.p3 + gridDim.x);
 }
 
 // The true residual's test.  True when the solve has ended (converged, at
 // the start or now, or at its iteration limit) and the caller's update is
 // due; else a new cycle starts.  Every block takes the same decision; block
 // 0 records it.
-__device__ __forceinline__ bool solve_ended(const GmBuf &gm, double *lds) {
+__device__ __forceinline__ bool solve_ended(const GmBuf &gm) {
+  __shared__ double rr[1];
+  __shared__ int how;  // 0: nothing to do; 1: ended at the start; 2: to be tested
   GmState *const st = gm.st;
-  const int done0 = st->done;
-  if (st->code != 0) return false;
-  if (done0 == kGmAtStart) return true;
-  if (st->end_at < 0) return false;
-  get_sums(gm.p3 + gm.na, gm.na, 1, lds);
-  const double beta = sqrt(lds[0]);
+  if (threadIdx.x == 0) how = st->code != 0 ? 0 : (st->done == kGmAtStart ? 1 : (st->end_at < 0 ? 0 : 2));
+  get_sums(gm.p3 + gm.na, gm.na, 1, rr);
+  if (how < 2) return how == 1;
+  const double beta = sqrt(rr[0]);
   const double bnorm = st->bnorm;
   const bool bad = !isfinite(beta);
   const bool conv = beta <= st->tol;
@@ -654,8 +941,7 @@ __device__ __forceinline__ bool solve_ended(const GmBuf &gm, double *lds) {
 template <int DIM>
 __global__ __launch_bounds__(TB) void k_gm_finish(KParams kp, GmBuf gm, const double *En, const double *Bn,
                                                   const double *__restrict__ Eth, double *En1, double *Bn1) {
-  __shared__ double lds[1];
-  if (!solve_ended(gm, lds)) return;
+  if (!solve_ended(gm)) return;
   const size_t N = (size_t)kp.ncells;
   const double th = kp.theta;
   const Groups gr = block_groups(node_groups(kp));
@@ -679,8 +965,7 @@ __global__ __launch_bounds__(TB) void k_gm_finish(KParams kp, GmBuf gm, const do
 template <int DIM>
 __global__ __launch_bounds__(TB) void k_gm_adj_finish(KParams kp, GmBuf gm, const double *lE1, const double *lB1,
                                                       const double *__restrict__ mu, double *lEn, double *lBn) {
-  __shared__ double lds[1];
-  if (!solve_ended(gm, lds)) return;
+  if (!solve_ended(gm)) return;
   const size_t N = (size_t)kp.ncells;
   const double th = kp.theta, ctdt = kp.c * kp.theta * kp.dt;
   const Groups gr = block_groups(node_groups(kp));
@@ -726,42 +1011,70 @@ template <int DIM, bool TR, typename MT>
 void gm_apply(const KParams &kp, const GmBuf &gm, const void *Mv, int j, bool cycle0, int nb, hipStream_t st) {
   const MT *M = static_cast<const MT *>(Mv);
   if (j == 0)
-    hipLaunchKernelGGL((k_gm_apply<DIM, TR, MT, 1, true>), dim3(nb), dim3(TB), 0, st, kp, gm, M, j, cycle0 ? 1 : 0);
+    hipLaunchKernelGGL((k_gm_apply<DIM, TR, MT, 1, true>), dim3(nb), dim3(kOpThreads<DIM>), 0, st, kp, gm, M, j,
+                       cycle0 ? 1 : 0);
   else if (j <= 8)
-    hipLaunchKernelGGL((k_gm_apply<DIM, TR, MT, 8, false>), dim3(nb), dim3(TB), 0, st, kp, gm, M, j, 0);
+    hipLaunchKernelGGL((k_gm_apply<DIM, TR, MT, 8, false>), dim3(nb), dim3(kOpThreads<DIM>), 0, st, kp, gm, M, j, 0);
   else if (j <= 16)
-    hipLaunchKernelGGL((k_gm_apply<DIM, TR, MT, 16, false>), dim3(nb), dim3(TB), 0, st, kp, gm, M, j, 0);
+    hipLaunchKernelGGL((k_gm_apply<DIM, TR, MT, 16, false>), dim3(nb), dim3(kOpThreads<DIM>), 0, st, kp, gm, M, j, 0);
   else if (j <= 32)
-    hipLaunchKernelGGL((k_gm_apply<DIM, TR, MT, 32, false>), dim3(nb), dim3(TB), 0, st, kp, gm, M, j, 0);
+    hipLaunchKernelGGL((k_gm_apply<DIM, TR, MT, 32, false>), dim3(nb), dim3(kOpThreads<DIM>), 0, st, kp, gm, M, j, 0);
   else
-    hipLaunchKernelGGL((k_gm_apply<DIM, TR, MT, 64, false>), dim3(nb), dim3(TB), 0, st, kp, gm, M, j, 0);
+    hipLaunchKernelGGL((k_gm_apply<DIM, TR, MT, 64, false>), dim3(nb), dim3(kOpThreads<DIM>), 0, st, kp, gm, M, j, 0);
 }
 
 void gm_residual(const KParams &kp, const GmBuf &gm, int mass_fp32, bool transpose, const void *M, const double *x,
                  bool start, hipStream_t st) {
-  const int nb = gm.na;
-  if (kp.dim == 3) hipLaunchKernelGGL(k_gm_curl, dim3(nb), dim3(TB), 0, st, kp, gm, x, start ? -2 : -1);
 #define RELSIM_RES(DIM, TR, MT)                                                                                       \
-  hipLaunchKernelGGL((k_gm_residual<DIM, TR, MT>), dim3(nb), dim3(TB), 0, st, kp, gm, static_cast<const MT *>(M), x, \
-                     start ? 1 : 0)
+  hipLaunchKernelGGL((k_gm_residual<DIM, TR, MT>), dim3(gm.na), dim3(kOpThreads<DIM>), 0, st, kp, gm,                 \
+                     static_cast<const MT *>(M), x, start ? 1 : 0)
   RELSIM_GM_MASS(RELSIM_RES);
 #undef RELSIM_RES
 }
 
 }  // namespace
 
-void launch_apply(const KParams &kp, int mass_fp32, bool transpose, const void *M, const double *x, const double *t,
-                  double *out, hipStream_t st) {
-  const int ng = node_groups(kp);
-#define RELSIM_APPLY(DIM, TR, MT)                                                               \
-  hipLaunchKernelGGL((k_apply<DIM, TR, MT>), dim3(ng), dim3(TB), 0, st, kp, static_cast<const MT *>(M), x, t, out)
+void launch_apply(const KParams &kp, int mass_fp32, bool transpose, const void *M, const double *x, double *y,
+                  hipStream_t st) {
+  const int nb = kp.dim == 2 ? node_groups(kp) : Tiles3(kp).count();
+#define RELSIM_APPLY(DIM, TR, MT)                                                                        \
+  hipLaunchKernelGGL((k_apply<DIM, TR, MT>), dim3(nb), dim3(kOpThreads<DIM>), 0, st, kp,                 \
+                     static_cast<const MT *>(M), x, y)
   RELSIM_GM_MASS(RELSIM_APPLY);
 #undef RELSIM_APPLY
 }
 
+// Tile extents of the 3D operator: rows of at most 62 nodes (a lane on either
+// side is the neighbour's), and the ty <= kRows3 rows and lz planes for which
+// the tiles read least, each with 9 of the 14 blocks of a row and of a plane
+// of its neighbours, while the tiles, one to a CU at a time, keep 85 % of the
+// 256 CUs busy; fewer busy CUs count against them in proportion.
+void plan_tiles3(KParams &kp) {
+  const int ntx = (kp.nx + 61) / 62;
+  kp.t3x = (kp.nx + ntx - 1) / ntx;
+  kp.t3y = kp.t3z = 0;
+  double best = 0.0;
+  for (int ty = kRows3 < kp.ny ? kRows3 : kp.ny; ty >= 1; --ty)
+    for (int lz = kp.nz; lz >= 1; --lz) {
+      const double tiles = (double)ntx * ((kp.ny + ty - 1) / ty) * ((kp.nz + lz - 1) / lz);
+      const double busy = tiles / (256.0 * ceil(tiles / 256.0)) / 0.85;
+      const double cost = tiles * (ty + 9.0 / 14.0) * (lz + 9.0 / 14.0) / (busy < 1.0 ? busy : 1.0);
+      if (kp.t3z == 0 || cost < best) {
+        best = cost;
+        kp.t3y = ty;
+        kp.t3z = lz;
+      }
+    }
+}
+
 void gm_blocks(const KParams &kp, GmBuf &gm) {
-  const int ng = node_groups(kp);
-  gm.na = ng < kGmNodeBlocks ? ng : kGmNodeBlocks;
+  if (kp.dim == 3) {
+    const int nt = Tiles3(kp).count();
+    gm.na = nt < kGmTileBlocks ? nt : kGmTileBlocks;
+  } else {
+    const int ng = node_groups(kp);
+    gm.na = ng < kGmNodeBlocks ? ng : kGmNodeBlocks;
+  }
   const size_t nv = (gm.ld / 2 + TB - 1) / TB;
   gm.no = nv < (size_t)kGmVecBlocks ? (int)nv : kGmVecBlocks;
 }
@@ -789,8 +1102,6 @@ void launch_gm_adj_start(const KParams &kp, const GmBuf &gm, const double *lth, 
 void launch_gm_apply(const KParams &kp, const GmBuf &gm, int mass_fp32, bool transpose, const void *M, int j,
                      bool cycle0, hipStream_t st) {
   const int nb = gm.na;
-  if (kp.dim == 3)
-    hipLaunchKernelGGL(k_gm_curl, dim3(nb), dim3(TB), 0, st, kp, gm, j == 0 ? gm.r : gm.V + (size_t)j * gm.ld, j);
 #define RELSIM_STEP(DIM, TR, MT) gm_apply<DIM, TR, MT>(kp, gm, M, j, cycle0, nb, st)
   RELSIM_GM_MASS(RELSIM_STEP);
 #undef RELSIM_STEP

@@ -18,6 +18,7 @@ struct KParams {
   int sty, stz;       // y and z extents of the push passes' segment tiles (the last ones may reach past the grid)
   int ltx, lty, ltz;  // their base-2 logarithms
   int ntx, nty;       // tiles along x and y
+  int t3x, t3y, t3z;  // tile extents of the 3D field operator (plan_tiles3)
   int gx, gxy;        // strides of the ghosted field copies: nx + 2, (nx + 2)(ny + 2)
   int nghost;         // points of a ghosted field copy
   double dx, dy, dz, dt, c, theta, V;
@@ -30,13 +31,14 @@ struct KParams {
 
 // Offsets (in bytes) of the regions carved out of the caller's workspace.
 struct Layout {
-  size_t S, cnt, pre, total, scan_tmp, dirc, err, gm_V, gm_t, gm_b, gm_r, gm_part, gm_state, red_part, red_res;
+  size_t S, cnt, pre, total, scan_tmp, dirc, err, gm_V, gm_b, gm_r, gm_part, gm_state, red_part, red_res;
   size_t gs_k0, gs_k1, gs_v0, gs_v1, gs_hist, stB, stE, sink, kin_part, push_ke, end;
 };
 
 constexpr int kMaxRestart = 64;
 constexpr int kGmThreads = 256;     // threads per block of the GMRES kernels
-constexpr int kGmNodeBlocks = 512;  // most blocks of the per-node GMRES kernels (a multiple of 8)
+constexpr int kGmNodeBlocks = 512;  // most blocks of the 2D operator's GMRES kernels (a multiple of 8)
+constexpr int kGmTileBlocks = 1024; // most blocks of the 3D operator's (a multiple of 8)
 constexpr int kGmVecBlocks = 512;   // most blocks of the others
 constexpr int kRedBlocks = 1024;    // blocks of the energy reductions
 constexpr int kSinkSlots = 512;     // per-lane store sinks of the particle kernels (power of two), 32 B each
@@ -218,26 +220,27 @@ struct GmState : GmHead {
   double H[kMaxRestart * (kMaxRestart + 1)], R[kMaxRestart * (kMaxRestart + 1)];
 };
 // The solve's buffers: V [m + 1] rows of n3 values with stride ld (even; the
-// pad is 0), vectors t, b, r; partial sums per block, [quantity][block]: p1
-// (2 kMaxRestart + 1 quantities) and p3 (2) by the per-node kernels, p2 (1)
-// by ortho.
+// pad is 0), vectors b, r; partial sums per block, [quantity][block]: p1
+// (2 kMaxRestart + 1 quantities) and p3 (2) by the kernels with the operator,
+// p2 (1) by ortho.
 struct GmBuf {
-  double *V, *t, *b, *r, *p1, *p2, *p3;
+  double *V, *b, *r, *p1, *p2, *p3;
   GmState *st;
   size_t n3, ld;
-  int na, no;  // blocks of the per-node kernels, and of ortho and update
+  int na, no;  // blocks of the kernels with the operator, and of ortho and update
   int m, maxit;
   double rtol;
 };
-// out = A x or A^T x, with t = C_NC x given in 3D (not read in 2D); M: the
-// stored half of the mass matrix, float if mass_fp32, else double
-void launch_apply(const KParams &kp, int mass_fp32, bool transpose, const void *M, const double *x, const double *t,
-                  double *out, hipStream_t st);
+// y = A x or A^T x; M: the stored half of the mass matrix, float if mass_fp32,
+// else double
+void launch_apply(const KParams &kp, int mass_fp32, bool transpose, const void *M, const double *x, double *y,
+                  hipStream_t st);
 // A solve is start (or adj_start), then apply(0), ortho(0), apply(1), ortho(1),
 // ..., apply(n) for n columns (apply(n) finds that column n - 1 was the last),
 // then update, residual and finish (or adj_finish).  Kernels past the end of
 // the cycle or of the solve do nothing, so more may be enqueued than are
 // needed; the head of the state says how far the solve came.
+void plan_tiles3(KParams &kp);                 // sets t3x, t3y, t3z
 void gm_blocks(const KParams &kp, GmBuf &gm);  // sets na, no
 void launch_gm_start(const KParams &kp, const GmBuf &gm, int mass_fp32, const void *M, const double *En,
                      const double *Bn, const double *J, const double *x0, double *x, const int32_t *flags,
