@@ -183,7 +183,7 @@ size_t max_push_waves(const relsim_params *p) {
   size_t most = 0;
   for (int C = 1; C <= 64; C *= 2)  // segments side by side in a tile: 16 / C
     most = std::max(most, padded((p->nx + C - 1) / C, C < 16 ? 16 / C : 1));
-  return most * padded(p->ny, push_tile_rows(p)) * (p->dim == 3 ? padded(p->nz, 4) : 1);
+  return most * padded(p->ny, push_tile_rows(p)) * (p->dim == 3 ? padded(p->nz, 4) : 1) + kMaxSplits;
 }
 
 Layout make_layout(const relsim_params *p) {
@@ -317,9 +317,10 @@ enum KernelKind { K_DEPOSIT, K_PUSH, K_SCATTER, K_OTHER };
 // for both).  The segments need not divide the row (its last one is shorter):
 // on the 625 x 625 sheet (42 per cell on average), whose rows only single
 // cells divide, segments of 8 and 4 cells took push and re-sort from 897 to
-// 745 us (8 and 8: 945, 16 and 4: 860), and on 91 x 47 x 33 cells from 658 to
+// 745 us (8 and 8: 945, 16 and 4: 860; 450 with the order and the splitting of
+// crowded segments in particles.hip), and on 91 x 47 x 33 cells from 658 to
 // 274 us.
-int choose_cells(const relsim_ctx *c, int64_t n, KernelKind k) {
+PushPlan plan_push(const relsim_ctx *c, int64_t n, KernelKind k) {
   const double rounds = k == K_SCATTER ? 4.0 : 8.0;
   const size_t lds = 8192;
   const double mean = (double)n / (double)c->kp.ncells;
@@ -327,7 +328,10 @@ int choose_cells(const relsim_ctx *c, int64_t n, KernelKind k) {
   while (C < 64 && 2.0 * C * mean <= rounds * 64.0 && 2 * C <= c->kp.nx && c->kp.ncells / (2 * C) >= 2048 &&
          push_lds_bytes(c->kp, c->p.precision, 2 * C) <= lds)
     C *= 2;
-  return C;
+  // a segment is crowded beyond twice the particles aimed at; one of a single
+  // cell is not split
+  const int64_t thr = std::max<int64_t>((int64_t)(2 * 64 * rounds), (n + kMaxSplits - 1) / kMaxSplits);
+  return {C, (int)n, C > 1 ? (int)thr : INT_MAX};
 }
 
 // Lanes per cell for the deposit and the kinetic-energy kernel: the largest
@@ -610,8 +614,7 @@ int relsim_push_ec(relsim_ctx *c, relsim_particles *pt, const double *E_theta, c
     return fail(c, RELSIM_EINVAL, "gbar not aligned to its element size");
   PartPtrs pp = front(pt);
   pp.gbar = gbar;
-  const int cells = choose_cells(c, pt->n, K_PUSH);
-  const int cells_s = choose_cells(c, pt->n, K_SCATTER);
+  const PushPlan plan = plan_push(c, pt->n, K_PUSH), plan_s = plan_push(c, pt->n, K_SCATTER);
   uint8_t *dirc = c->at<uint8_t>(c->L.dirc);
   uint16_t *cnt = c->at<uint16_t>(c->L.cnt);
   uint16_t *pre = c->at<uint16_t>(c->L.pre);
@@ -626,7 +629,7 @@ int relsim_push_ec(relsim_ctx *c, relsim_particles *pt, const double *E_theta, c
   // with resort the first pass only counts the moves, and the second pushes
   // again, writing the new state straight into its new place
   timed(c, resort ? "push_count" : "push", [&] {
-    launch_push(c->kp, c->p.precision, cells, pp, stE, stB, dirc, cnt, err, resort ? 1 : 0,
+    launch_push(c->kp, c->p.precision, plan, pp, stE, stB, dirc, cnt, err, resort ? 1 : 0,
                 c->at<char>(c->L.sink), c->st);
   });
   if (resort) {
@@ -635,14 +638,14 @@ int relsim_push_ec(relsim_ctx *c, relsim_particles *pt, const double *E_theta, c
       launch_scan(total, pt->bin_start_back, c->kp.nbins, c->at<int32_t>(c->L.scan_tmp), c->st);
     });
     timed(c, "push_scatter", [&] {
-      launch_push_scatter(c->kp, c->p.precision, cells_s, pp, stE, stB, dirc, pre, pt->bin_start_back, back(pt),
+      launch_push_scatter(c->kp, c->p.precision, plan_s, pp, stE, stB, dirc, pre, pt->bin_start_back, back(pt),
                           (int)pt->n, err, clamp_counter(c), new_index, c->at<char>(c->L.sink),
                           c->at<double>(c->L.push_ke), c->st);
     });
     rc = launch_status(c, "relsim_push");
     if (rc) return rc;
     swap_sets(pt);
-    c->push_ke_parts = push_waves(c->kp, cells_s);
+    c->push_ke_parts = push_waves(c->kp, plan_s);
     return RELSIM_OK;
   }
   c->push_ke_parts = 0;
@@ -660,7 +663,7 @@ int relsim_gamma_mean(relsim_ctx *c, const relsim_particles *pt, const double *E
   if ((gbar && !aligned(gbar, es)) || !aligned(gbar_next, es))
     return fail(c, RELSIM_EINVAL, "gbar not aligned to its element size");
   if (gbar && gbar == gbar_next) return fail(c, RELSIM_EINVAL, "gbar and gbar_next must not alias");
-  const int cells = choose_cells(c, pt->n, K_PUSH);
+  const PushPlan plan = plan_push(c, pt->n, K_PUSH);
   int32_t *err = c->at<int32_t>(c->L.err);
   // the 8 bytes after the error flags (both in the 64-byte flag slot)
   unsigned long long *chg = reinterpret_cast<unsigned long long *>(c->at<char>(c->L.err) + 8);
@@ -674,7 +677,7 @@ int relsim_gamma_mean(relsim_ctx *c, const relsim_particles *pt, const double *E
     launch_stage_field(c->kp, c->p.precision, E_theta, stE, c->st);
   });
   timed(c, "gamma_mean", [&] {
-    launch_gamma_mean(c->kp, c->p.precision, cells, pp, stE, stB, err, c->at<char>(c->L.sink), gbar_next, chg,
+    launch_gamma_mean(c->kp, c->p.precision, plan, pp, stE, stB, err, c->at<char>(c->L.sink), gbar_next, chg,
                       c->st);
   });
   rc = launch_status(c, "relsim_gamma_mean");

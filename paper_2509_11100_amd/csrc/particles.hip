@@ -865,44 +865,74 @@ __device__ __forceinline__ void push_one(const KParams &kp, const PC<T> &pc, con
 // ---------------------------------------------------------------------------
 template <typename T, int DIM>
 struct Segment {
-  int C, nb;         // cells and bins of the segment
-  int c0, i0, j, k;  // first cell and its coordinates
+  int C;             // cells of the segment
+  int nb;            // bins of the segment, or of a wave's part of it
+  int c0, i0, j, k;  // first cell (of the segment or the part) and its coordinates
   V4<T> *Bg;         // (C + 2) x 3 [x 3] cell centres from (i0 - 1, j - 1, k - 1), x fastest
   V4<T> *Eg;         // (C + 1) x 2 [x 2] nodes from (i0, j, k)
   T (*stab)[8];      // species charge and beta
   double *mtab;      // species mass (FP64)
-  int *binb;         // nb + 1 bin starts, then INT_MAX up to a power of two
+  int *binb;         // nb + 1 bin starts, then INT_MAX up to binb_slots
   int *keys;         // nb x NDIR counters (counting pass) or run bases (scatter)
 };
 
 // How the push passes' segments of C cells (the last one of a row may be
 // shorter) tile the grid: spr segments side by side in a tile, ntx x nty x
 // ntz tiles of spr x sty x stz segments (see make_kparams), the last ones
-// possibly reaching past the grid.
+// possibly reaching past the grid.  Worked out on the host: the divisions took
+// a wave about as long as a round of particles.
 struct SegTiles {
+  int C, nseg;              // cells of a segment, segments of a row
   int spr, ntx, nty, ntz;
-  __host__ __device__ SegTiles(const KParams &kp, int C) {
-    const int nseg = (kp.nx + C - 1) / C;
-    spr = even_tile(nseg, C < 16 ? 16 / C : 1);
-    ntx = (nseg + spr - 1) / spr;
-    nty = (kp.ny + kp.sty - 1) / kp.sty;
-    ntz = (kp.nz + kp.stz - 1) / kp.stz;
-  }
+  int chunk;                // segments that an XCD takes at a time
+  int thr, ns;              // particles beyond which a segment is split, waves added for that
 };
-// The wave's place in that order: an XCD takes up to 4 tiles at a time (a
+// Crowded segments.  Sheets hold up to 17 times the particles of their
+// surroundings, and the segments are sized for the mean, so a segment with
+// more than thr particles is split into parts of whole cells, one wave each:
+// as many as there are multiples of thr in its particle range, and one.  The
+// launch has, ahead of the segments' own waves, one wave for every multiple of
+// thr below n; it looks up the segment that holds that particle and takes the
+// part that falls to it, or has nothing to do (almost all of them, where no
+// segment is crowded: thr is at least n / kMaxSplits).  214 x 371
+// reconnection sheet, 306 particles per cell in 24 rows and 18 in the others:
+// push and re-sort 474 us
+// without, 207 with (the added waves after the others instead of ahead of
+// them: 240); 625 x 625 sheet 635 -> 450; 256 x 128 pair plasma, 32 per cell,
+// where nothing is crowded, 94 -> 76 (the host's share of the divisions).
+struct WavePart {
+  int seg, part;  // segment (in the order of stage_segment); its part, 0 for the segment's own wave, or -1: nothing to do
+};
+// multiples of thr in [beg, end)
+__device__ __forceinline__ int multiples(int beg, int end, int thr) {
+  return end > beg ? (end - 1) / thr - (beg > 0 ? (beg - 1) / thr : -1) : 0;
+}
+__device__ __forceinline__ int segment_parts(int beg, int end, int thr) {
+  return end - beg > thr ? 1 + multiples(beg, end, thr) : 1;
+}
+
+// The order in which the XCDs take the segments: an XCD takes up to 4 tiles at a time (a
 // fourth of its tiles on small grids).  With one contiguous band per XCD
 // instead, the rows of a current sheet, which hold most of the particles of
 // the 625 x 625 reconnection run, fall to two XCDs: push and re-sort 745 us
 // there, 635 with 4 tiles at a time (1, 2, 16, 64: 640, 640, 660, 730); 2618,
 // 2520 (2535, 2510, 2600, 2658) on the 256 x 128 x 128 sheet.
-__device__ __forceinline__ int segment_wave(const KParams &kp, int C, int b, int nb) {
-  const SegTiles t(kp, C);
+SegTiles seg_tiles(const KParams &kp, const PushPlan &pl) {
+  SegTiles t;
+  t.C = pl.cells;
+  t.nseg = (kp.nx + t.C - 1) / t.C;
+  t.spr = even_tile(t.nseg, t.C < 16 ? 16 / t.C : 1);
+  t.ntx = (t.nseg + t.spr - 1) / t.spr;
+  t.nty = (kp.ny + kp.sty - 1) / kp.sty;
+  t.ntz = (kp.nz + kp.stz - 1) / kp.stz;
   const int tiles = t.ntx * t.nty * t.ntz >> 5;
-  return xcd_chunk(b, nb, (tiles < 1 ? 1 : (tiles < 4 ? tiles : 4)) * t.spr * kp.sty * kp.stz);
+  t.chunk = (tiles < 1 ? 1 : (tiles < 4 ? tiles : 4)) * t.spr * kp.sty * kp.stz;
+  t.thr = pl.thr;
+  t.ns = pl.n > pl.thr ? (pl.n - 1) / pl.thr + 1 : 0;
+  return t;
 }
-__host__ inline int segment_waves(const KParams &kp, int C) {
-  const SegTiles t(kp, C);
-  return t.ntx * t.spr * t.nty * kp.sty * t.ntz * kp.stz;
+int seg_waves(const KParams &kp, const SegTiles &t) {
+  return t.ns + t.ntx * t.spr * t.nty * kp.sty * t.ntz * kp.stz;
 }
 
 // Smallest power of two >= nb (nb >= 1).
@@ -912,9 +942,10 @@ __host__ __device__ constexpr int pow2_at_least(int nb) {
   return q;
 }
 
-// Slots of the staged bin starts: nb + 1 starts, padded to a power of two so
-// that the bin search needs no bounds check.
-__host__ __device__ constexpr int binb_slots(int nb) { return nb + 1 > pow2_at_least(nb) ? nb + 1 : pow2_at_least(nb); }
+// Slots of the staged bin starts: the nb bins' starts and their end, padded so
+// that the bin search, which probes a power of two of bins from the first one
+// of a wave's part on, needs no bounds check.
+__host__ __device__ constexpr int binb_slots(int nb) { return nb + 1 + pow2_at_least(nb); }
 
 // LDS bytes of a segment of C cells with S species.
 template <typename T, int DIM>
@@ -925,7 +956,7 @@ __host__ __device__ constexpr size_t segment_lds_bytes(int C, int S) {
 }
 
 template <typename T, int DIM>
-__device__ __forceinline__ Segment<T, DIM> stage_segment(const KParams &kp, int C, int wave, const PC<T> &pc,
+__device__ __forceinline__ Segment<T, DIM> stage_segment(const KParams &kp, const SegTiles &tl, int wave, const PC<T> &pc,
                                                          const int32_t *__restrict__ bin_start,
                                                          const V4<T> *__restrict__ Es, const V4<T> *__restrict__ Bs,
                                                          unsigned char *smem, int lane) {
@@ -935,7 +966,7 @@ __device__ __forceinline__ Segment<T, DIM> stage_segment(const KParams &kp, int 
   // segments row-major inside a tile), as the other particle kernels visit
   // cells: the destinations of neighbouring sources are then written close
   // together in time
-  const SegTiles tl(kp, C);
+  int C = tl.C;
   const int per_tile = tl.spr * kp.sty * kp.stz;
   const int tile = wave / per_tile, r = wave - tile * per_tile;
   const int t2 = tile / tl.ntx;
@@ -1010,11 +1041,68 @@ __device__ __forceinline__ Segment<T, DIM> stage_segment(const KParams &kp, int 
   return sg;
 }
 
+// The segment of C cells (row-major, nseg to a row) that holds particle p: the
+// last one that starts at or before it, 64 probes at a time.
+__device__ __forceinline__ int segment_holding(const KParams &kp, int C, int nseg, int p,
+                                               const int32_t *__restrict__ bin_start, int lane) {
+  int lo = 0, count = nseg * kp.ny * kp.nz;
+  while (count > 1) {
+    const int step = (count + 63) >> 6;
+    const int z = lo + min(lane * step, count - 1);
+    const int row = z / nseg;
+    const bool at = bin_start[(row * kp.nx + (z - row * nseg) * C) * kp.nspecies] <= p;
+    // the starts do not decrease: the lanes that are at or before p are the first ones
+    const int last = __popcll(__ballot(at)) - 1;
+    const int off = min(last * step, count - 1);
+    lo += off;
+    count = min(step, count - off);
+  }
+  return lo;
+}
+
+// Which segment and part the block's wave takes.
+__device__ __forceinline__ WavePart wave_work(const KParams &kp, const SegTiles &tl,
+                                              const int32_t *__restrict__ bin_start, int lane) {
+  const int b = (int)blockIdx.x;
+  if (b >= tl.ns) return {xcd_chunk(b - tl.ns, (int)gridDim.x - tl.ns, tl.chunk), 0};
+  const int p = b * tl.thr;
+  const int z = __builtin_amdgcn_readfirstlane(segment_holding(kp, tl.C, tl.nseg, p, bin_start, lane));
+  const int row = z / tl.nseg, s = z - row * tl.nseg, i0 = s * tl.C, cells = min(tl.C, kp.nx - i0);
+  const int first = (row * kp.nx + i0) * kp.nspecies;
+  const int beg = bin_start[first], end = bin_start[first + cells * kp.nspecies];
+  // p is the k-th multiple of thr in the segment: part k + 1
+  const int part = 1 + multiples(beg, p, tl.thr);
+  if (part >= segment_parts(beg, end, tl.thr) || part >= cells) return {0, -1};
+  // the segment's place in the order of stage_segment
+  const int j = row % kp.ny, k = row / kp.ny;
+  const int tile = s / tl.spr + tl.ntx * (j / kp.sty + tl.nty * (k / kp.stz));
+  return {tile * (tl.spr * kp.sty * kp.stz) + s % tl.spr + tl.spr * (j % kp.sty + kp.sty * (k % kp.stz)), part};
+}
+
+// The part of a staged segment that a wave walks.
+template <typename T, int DIM>
+__device__ __forceinline__ Segment<T, DIM> segment_part(Segment<T, DIM> sg, int S, int thr, int part) {
+  const int beg = __builtin_amdgcn_readfirstlane(sg.binb[0]), end = __builtin_amdgcn_readfirstlane(sg.binb[sg.nb]);
+  if (end - beg <= thr) return sg;
+  const int parts = min(segment_parts(beg, end, thr), sg.C);
+  const int per = (sg.C + parts - 1) / parts;
+  const int c = __builtin_amdgcn_readfirstlane(min(part * per, sg.C));
+  const int n = __builtin_amdgcn_readfirstlane(min(per, sg.C - c));
+  sg.Bg += c;
+  sg.Eg += c;
+  sg.binb += c * S;
+  sg.keys += c * S * (DIM == 3 ? 27 : 9);
+  sg.c0 += c;
+  sg.i0 += c;
+  sg.nb = n * S;
+  return sg;
+}
+
 // Bin (within the segment) of particle p, binb[0] <= p < binb[nb]: the last
-// b with binb[b] <= p, by binary search over the staged bin starts.  The
-// starts are padded with INT_MAX up to a power of two, so every probe reads
-// a valid slot and the search is straight-line code (a wave-uniform number
-// of steps, no lane-dependent branch).
+// b with binb[b] <= p, by binary search over the staged bin starts.  Probes
+// past binb[nb] read later starts or the INT_MAX padding, all above p, so the
+// search is straight-line code (a wave-uniform number of steps, no
+// lane-dependent branch).
 __device__ __forceinline__ int segment_bin(const int *binb, int nb, int p) {
   int lo = 0;
   for (int step = pow2_at_least(nb) >> 1; step > 0; step >>= 1) {
@@ -1067,7 +1155,7 @@ __device__ __forceinline__ CellFields<T> segment_fields(const Segment<T, DIM> &s
 //      an integer atomic max orders them; infinite if not finite)
 //   3  as 2 with gbar = gamma(u^n) (the iteration's start; gb unused)
 template <typename T, int DIM, bool COUNT, int GB>
-__global__ __launch_bounds__(64) void k_push(KParams kp, int C, const int32_t *__restrict__ bin_start,
+__global__ __launch_bounds__(64) void k_push(KParams kp, SegTiles tl, const int32_t *__restrict__ bin_start,
                                              V2<T> *__restrict__ xy, V4<T> *__restrict__ uw, T *__restrict__ zz,
                                              const V4<T> *__restrict__ Es, const V4<T> *__restrict__ Bs,
                                              uint8_t *__restrict__ dirc, uint16_t *__restrict__ cnt,
@@ -1081,13 +1169,15 @@ __global__ __launch_bounds__(64) void k_push(KParams kp, int C, const int32_t *_
   extern __shared__ __attribute__((aligned(32))) unsigned char smem[];
   const int lane = threadIdx.x;
   const PC<T> pc(kp);
-  const int wave = segment_wave(kp, C, blockIdx.x, gridDim.x);
-  const Segment<T, DIM> sg = stage_segment<T, DIM>(kp, C, wave, pc, bin_start, Es, Bs, smem, lane);
-  if (sg.C == 0) return;
-  if constexpr (COUNT)
-    for (int t = lane; t < sg.nb * NDIR; t += 64) sg.keys[t] = 0;
-  __syncthreads();
   const int S = kp.nspecies;
+  const WavePart work = wave_work(kp, tl, bin_start, lane);
+  if (work.part < 0) return;
+  const Segment<T, DIM> whole = stage_segment<T, DIM>(kp, tl, work.seg, pc, bin_start, Es, Bs, smem, lane);
+  if (whole.C == 0) return;
+  if constexpr (COUNT)
+    for (int t = lane; t < whole.nb * NDIR; t += 64) whole.keys[t] = 0;
+  __syncthreads();
+  const Segment<T, DIM> sg = segment_part<T, DIM>(whole, S, tl.thr, work.part);
   const T sq0 = pc.q0, sq1 = pc.q1, sb0 = pc.b0, sb1 = pc.b1;
   T *const sinkT = sink_slot<T>(sink, lane);
   uint8_t *const sinkB = sink_slot<uint8_t>(sink, lane);
@@ -1308,7 +1398,7 @@ __device__ __forceinline__ void scatter_round(const KParams &kp, const PC<T> &pc
 // is thus read twice and written once per step.
 // ---------------------------------------------------------------------------
 template <typename T, int DIM, bool PERM, bool GB>
-__global__ __launch_bounds__(64) void k_push_scatter(KParams kp, int C, const int32_t *__restrict__ bin_start,
+__global__ __launch_bounds__(64) void k_push_scatter(KParams kp, SegTiles tl, const int32_t *__restrict__ bin_start,
                                                      const V2<T> *__restrict__ xy,
                                                      const V4<T> *__restrict__ uw, const T *__restrict__ zz,
                                                      const V4<T> *__restrict__ Es, const V4<T> *__restrict__ Bs,
@@ -1324,13 +1414,22 @@ __global__ __launch_bounds__(64) void k_push_scatter(KParams kp, int C, const in
   extern __shared__ __attribute__((aligned(32))) unsigned char smem[];
   const int lane = threadIdx.x;
   const PC<T> pc(kp);
-  const int wave = segment_wave(kp, C, blockIdx.x, gridDim.x);
-  const Segment<T, DIM> sg = stage_segment<T, DIM>(kp, C, wave, pc, bin_start, Es, Bs, smem, lane);
-  if (sg.C == 0) {
-    if (lane == 0) kep[wave] = 0.0;
+  const int S = kp.nspecies;
+  const WavePart work = wave_work(kp, tl, bin_start, lane);
+  // the partial kinetic sums: first those of the parts split off, then the
+  // segments' own in their order
+  double *const kew = kep + ((int)blockIdx.x < tl.ns ? (int)blockIdx.x : tl.ns + work.seg);
+  if (work.part < 0) {
+    if (lane == 0) *kew = 0.0;
     return;
   }
-  const int S = kp.nspecies;
+  const Segment<T, DIM> whole = stage_segment<T, DIM>(kp, tl, work.seg, pc, bin_start, Es, Bs, smem, lane);
+  if (whole.C == 0) {
+    if (lane == 0) *kew = 0.0;
+    return;
+  }
+  __syncthreads();
+  const Segment<T, DIM> sg = segment_part<T, DIM>(whole, S, tl.thr, work.part);
   const size_t nbins = (size_t)kp.nbins;
   // one lane per bin of the segment, all moves at once: the 2 NDIR loads
   // of a lane are in flight together, and for each move the lanes read
@@ -1408,7 +1507,7 @@ __global__ __launch_bounds__(64) void k_push_scatter(KParams kp, int C, const in
   // with the same value), one partial per segment
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) ke += __shfl_xor(ke, o);
-  if (lane == 0) kep[wave] = ke;
+  if (lane == 0) *kew = ke;
 }
 
 // ---------------------------------------------------------------------------
@@ -1561,70 +1660,72 @@ void deposit3_impl(const KParams &kp, const PartPtrs &pp, const void *Bst, void 
 }
 
 template <typename T, int DIM, bool COUNT, int GB>
-void push_launch(const KParams &kp, int C, const PartPtrs &pp, const void *Est, const void *Bst, uint8_t *dirc,
+void push_launch(const KParams &kp, PushPlan pl, const PartPtrs &pp, const void *Est, const void *Bst, uint8_t *dirc,
                  uint16_t *cnt, int32_t *err, void *sink, void *gnx, unsigned long long *chg, hipStream_t st) {
-  const int nblk = segment_waves(kp, C);
-  const size_t lds = segment_lds_bytes<T, DIM>(C, kp.nspecies);
-  hipLaunchKernelGGL((k_push<T, DIM, COUNT, GB>), dim3(nblk), dim3(64), lds, st, kp, C, pp.bin_start,
+  const SegTiles tl = seg_tiles(kp, pl);
+  const int nblk = seg_waves(kp, tl);
+  const size_t lds = segment_lds_bytes<T, DIM>(pl.cells, kp.nspecies);
+  hipLaunchKernelGGL((k_push<T, DIM, COUNT, GB>), dim3(nblk), dim3(64), lds, st, kp, tl, pp.bin_start,
                      mp<V2<T>>(pp.xy), mp<V4<T>>(pp.uw), mp<T>(pp.z), cp<V4<T>>(Est), cp<V4<T>>(Bst), dirc, cnt, err,
                      sink, cp<T>(pp.gbar), mp<T>(gnx), chg);
 }
 
 template <typename T, int DIM>
-void push_impl(const KParams &kp, int C, const PartPtrs &pp, const void *Est, const void *Bst, uint8_t *dirc,
+void push_impl(const KParams &kp, PushPlan pl, const PartPtrs &pp, const void *Est, const void *Bst, uint8_t *dirc,
                uint16_t *cnt, int32_t *err, int count_moves, void *sink, hipStream_t st) {
   if (pp.gbar) {
     if (count_moves)
-      push_launch<T, DIM, true, 1>(kp, C, pp, Est, Bst, dirc, cnt, err, sink, nullptr, nullptr, st);
+      push_launch<T, DIM, true, 1>(kp, pl, pp, Est, Bst, dirc, cnt, err, sink, nullptr, nullptr, st);
     else
-      push_launch<T, DIM, false, 1>(kp, C, pp, Est, Bst, dirc, cnt, err, sink, nullptr, nullptr, st);
+      push_launch<T, DIM, false, 1>(kp, pl, pp, Est, Bst, dirc, cnt, err, sink, nullptr, nullptr, st);
   } else {
     if (count_moves)
-      push_launch<T, DIM, true, 0>(kp, C, pp, Est, Bst, dirc, cnt, err, sink, nullptr, nullptr, st);
+      push_launch<T, DIM, true, 0>(kp, pl, pp, Est, Bst, dirc, cnt, err, sink, nullptr, nullptr, st);
     else
-      push_launch<T, DIM, false, 0>(kp, C, pp, Est, Bst, dirc, cnt, err, sink, nullptr, nullptr, st);
+      push_launch<T, DIM, false, 0>(kp, pl, pp, Est, Bst, dirc, cnt, err, sink, nullptr, nullptr, st);
   }
 }
 
 template <typename T, int DIM>
-void gamma_mean_impl(const KParams &kp, int C, const PartPtrs &pp, const void *Est, const void *Bst, int32_t *err,
+void gamma_mean_impl(const KParams &kp, PushPlan pl, const PartPtrs &pp, const void *Est, const void *Bst, int32_t *err,
                      void *sink, void *gnx, unsigned long long *chg, hipStream_t st) {
   if (pp.gbar)
-    push_launch<T, DIM, false, 2>(kp, C, pp, Est, Bst, nullptr, nullptr, err, sink, gnx, chg, st);
+    push_launch<T, DIM, false, 2>(kp, pl, pp, Est, Bst, nullptr, nullptr, err, sink, gnx, chg, st);
   else
-    push_launch<T, DIM, false, 3>(kp, C, pp, Est, Bst, nullptr, nullptr, err, sink, gnx, chg, st);
+    push_launch<T, DIM, false, 3>(kp, pl, pp, Est, Bst, nullptr, nullptr, err, sink, gnx, chg, st);
 }
 
 template <typename T, int DIM, bool PERM, bool GB>
-void scatter_launch(const KParams &kp, int C, const PartPtrs &src, const void *Est, const void *Bst,
+void scatter_launch(const KParams &kp, PushPlan pl, const PartPtrs &src, const void *Est, const void *Bst,
                     const uint8_t *dirc, const uint16_t *pre, const int32_t *bsn, const PartPtrs &out, int ntot,
                     int32_t *err, unsigned long long *clamps, int32_t *perm, void *sink, double *kep,
                     hipStream_t st) {
-  const int nblk = segment_waves(kp, C);
-  const size_t lds = segment_lds_bytes<T, DIM>(C, kp.nspecies);
-  hipLaunchKernelGGL((k_push_scatter<T, DIM, PERM, GB>), dim3(nblk), dim3(64), lds, st, kp, C, src.bin_start,
+  const SegTiles tl = seg_tiles(kp, pl);
+  const int nblk = seg_waves(kp, tl);
+  const size_t lds = segment_lds_bytes<T, DIM>(pl.cells, kp.nspecies);
+  hipLaunchKernelGGL((k_push_scatter<T, DIM, PERM, GB>), dim3(nblk), dim3(64), lds, st, kp, tl, src.bin_start,
                      cp<V2<T>>(src.xy), cp<V4<T>>(src.uw), cp<T>(src.z), cp<V4<T>>(Est), cp<V4<T>>(Bst), dirc, pre,
                      bsn, mp<V2<T>>(out.xy), mp<V4<T>>(out.uw), mp<T>(out.z), ntot, err, clamps, perm, sink,
                      cp<T>(src.gbar), kep);
 }
 
 template <typename T, int DIM>
-void scatter_impl(const KParams &kp, int C, const PartPtrs &src, const void *Est, const void *Bst,
+void scatter_impl(const KParams &kp, PushPlan pl, const PartPtrs &src, const void *Est, const void *Bst,
                   const uint8_t *dirc, const uint16_t *pre, const int32_t *bsn, const PartPtrs &out, int ntot,
                   int32_t *err, unsigned long long *cl, int32_t *perm, void *sink, double *kep, hipStream_t st) {
   if (src.gbar) {
     if (perm)
-      scatter_launch<T, DIM, true, true>(kp, C, src, Est, Bst, dirc, pre, bsn, out, ntot, err, cl, perm, sink, kep,
+      scatter_launch<T, DIM, true, true>(kp, pl, src, Est, Bst, dirc, pre, bsn, out, ntot, err, cl, perm, sink, kep,
                                          st);
     else
-      scatter_launch<T, DIM, false, true>(kp, C, src, Est, Bst, dirc, pre, bsn, out, ntot, err, cl, perm, sink,
+      scatter_launch<T, DIM, false, true>(kp, pl, src, Est, Bst, dirc, pre, bsn, out, ntot, err, cl, perm, sink,
                                           kep, st);
   } else {
     if (perm)
-      scatter_launch<T, DIM, true, false>(kp, C, src, Est, Bst, dirc, pre, bsn, out, ntot, err, cl, perm, sink,
+      scatter_launch<T, DIM, true, false>(kp, pl, src, Est, Bst, dirc, pre, bsn, out, ntot, err, cl, perm, sink,
                                           kep, st);
     else
-      scatter_launch<T, DIM, false, false>(kp, C, src, Est, Bst, dirc, pre, bsn, out, ntot, err, cl, perm, sink,
+      scatter_launch<T, DIM, false, false>(kp, pl, src, Est, Bst, dirc, pre, bsn, out, ntot, err, cl, perm, sink,
                                            kep, st);
   }
 }
@@ -1709,7 +1810,8 @@ void launch_assemble(const KParams &kp, int prec, int mass_fp32, const void *S, 
     assemble_as<float, double>(kp, S, J, M, st);
 }
 
-int push_waves(const KParams &kp, int cells) { return segment_waves(kp, cells); }
+
+int push_waves(const KParams &kp, const PushPlan &pl) { return seg_waves(kp, seg_tiles(kp, pl)); }
 
 size_t push_lds_bytes(const KParams &kp, int prec, int cells) {
   const bool f = prec == RELSIM_MIXED;
@@ -1718,25 +1820,25 @@ size_t push_lds_bytes(const KParams &kp, int prec, int cells) {
   return f ? segment_lds_bytes<float, 2>(cells, kp.nspecies) : segment_lds_bytes<double, 2>(cells, kp.nspecies);
 }
 
-void launch_push(const KParams &kp, int prec, int cells, const PartPtrs &pp, const void *Est, const void *Bst,
+void launch_push(const KParams &kp, int prec, const PushPlan &pl, const PartPtrs &pp, const void *Est, const void *Bst,
                  uint8_t *dirc, uint16_t *cnt, int32_t *err, int count_moves, void *sink, hipStream_t st) {
   const bool f = prec == RELSIM_MIXED;
   if (kp.dim == 3)
-    return f ? push_impl<float, 3>(kp, cells, pp, Est, Bst, dirc, cnt, err, count_moves, sink, st)
-             : push_impl<double, 3>(kp, cells, pp, Est, Bst, dirc, cnt, err, count_moves, sink, st);
-  return f ? push_impl<float, 2>(kp, cells, pp, Est, Bst, dirc, cnt, err, count_moves, sink, st)
-           : push_impl<double, 2>(kp, cells, pp, Est, Bst, dirc, cnt, err, count_moves, sink, st);
+    return f ? push_impl<float, 3>(kp, pl, pp, Est, Bst, dirc, cnt, err, count_moves, sink, st)
+             : push_impl<double, 3>(kp, pl, pp, Est, Bst, dirc, cnt, err, count_moves, sink, st);
+  return f ? push_impl<float, 2>(kp, pl, pp, Est, Bst, dirc, cnt, err, count_moves, sink, st)
+           : push_impl<double, 2>(kp, pl, pp, Est, Bst, dirc, cnt, err, count_moves, sink, st);
 }
 
-void launch_gamma_mean(const KParams &kp, int prec, int cells, const PartPtrs &pp, const void *Est,
+void launch_gamma_mean(const KParams &kp, int prec, const PushPlan &pl, const PartPtrs &pp, const void *Est,
                        const void *Bst, int32_t *err, void *sink, void *gbar_next, unsigned long long *chg,
                        hipStream_t st) {
   const bool f = prec == RELSIM_MIXED;
   if (kp.dim == 3)
-    return f ? gamma_mean_impl<float, 3>(kp, cells, pp, Est, Bst, err, sink, gbar_next, chg, st)
-             : gamma_mean_impl<double, 3>(kp, cells, pp, Est, Bst, err, sink, gbar_next, chg, st);
-  return f ? gamma_mean_impl<float, 2>(kp, cells, pp, Est, Bst, err, sink, gbar_next, chg, st)
-           : gamma_mean_impl<double, 2>(kp, cells, pp, Est, Bst, err, sink, gbar_next, chg, st);
+    return f ? gamma_mean_impl<float, 3>(kp, pl, pp, Est, Bst, err, sink, gbar_next, chg, st)
+             : gamma_mean_impl<double, 3>(kp, pl, pp, Est, Bst, err, sink, gbar_next, chg, st);
+  return f ? gamma_mean_impl<float, 2>(kp, pl, pp, Est, Bst, err, sink, gbar_next, chg, st)
+           : gamma_mean_impl<double, 2>(kp, pl, pp, Est, Bst, err, sink, gbar_next, chg, st);
 }
 
 namespace {
@@ -1791,19 +1893,19 @@ void launch_scan(const int32_t *in, int32_t *out, int n, int32_t *tmp, hipStream
   if (nb > 1) hipLaunchKernelGGL(k_scan_add, dim3((n + 255) / 256), dim3(256), 0, st, out, n, tmp);
 }
 
-void launch_push_scatter(const KParams &kp, int prec, int cells, const PartPtrs &src, const void *Est,
+void launch_push_scatter(const KParams &kp, int prec, const PushPlan &pl, const PartPtrs &src, const void *Est,
                          const void *Bst, const uint8_t *dirc, const uint16_t *pre, const int32_t *bin_start_new,
                          const PartPtrs &out, int ntot, int32_t *err, unsigned long long *clamps, int32_t *perm,
                          void *sink, double *kep, hipStream_t st) {
   const bool f = prec == RELSIM_MIXED;
   if (kp.dim == 3)
-    return f ? scatter_impl<float, 3>(kp, cells, src, Est, Bst, dirc, pre, bin_start_new, out, ntot, err, clamps,
+    return f ? scatter_impl<float, 3>(kp, pl, src, Est, Bst, dirc, pre, bin_start_new, out, ntot, err, clamps,
                                       perm, sink, kep, st)
-             : scatter_impl<double, 3>(kp, cells, src, Est, Bst, dirc, pre, bin_start_new, out, ntot, err, clamps,
+             : scatter_impl<double, 3>(kp, pl, src, Est, Bst, dirc, pre, bin_start_new, out, ntot, err, clamps,
                                        perm, sink, kep, st);
-  return f ? scatter_impl<float, 2>(kp, cells, src, Est, Bst, dirc, pre, bin_start_new, out, ntot, err, clamps,
+  return f ? scatter_impl<float, 2>(kp, pl, src, Est, Bst, dirc, pre, bin_start_new, out, ntot, err, clamps,
                                     perm, sink, kep, st)
-           : scatter_impl<double, 2>(kp, cells, src, Est, Bst, dirc, pre, bin_start_new, out, ntot, err, clamps,
+           : scatter_impl<double, 2>(kp, pl, src, Est, Bst, dirc, pre, bin_start_new, out, ntot, err, clamps,
                                      perm, sink, kep, st);
 }
 

@@ -137,22 +137,28 @@ void launch_deposit_cells(const KParams &kp, int prec, int group, const PartPtrs
                           hipStream_t st);
 void launch_assemble(const KParams &kp, int prec, int mass_fp32, const void *S, double *J, void *M,
                      hipStream_t st);
+constexpr int kMaxSplits = 8192;  // most waves that a push pass adds for crowded segments
 // `sink`: kSinkSlots * 64 * 32 bytes of workspace that lanes without a
 // particle store into (contents meaningless)
-// The push passes give each wave `cells` (a power of two) consecutive cells
-// of one grid row, the last segment of a row possibly fewer; push_waves is
-// the number of waves and push_lds_bytes the LDS one of them stages.
+// How a push pass is cut up: a wave takes `cells` (a power of two) consecutive
+// cells of one grid row, the last segment of a row possibly fewer, and a
+// segment with more than thr of the n particles is split over several waves.
+// push_waves is the number of waves and push_lds_bytes the LDS one of them
+// stages.
 // count_moves: only read the particles and write each one's move (dirc) and
 // the per-(move, bin) counts (first pass of the re-sort); else push in place
-int push_waves(const KParams &kp, int cells);
+struct PushPlan {
+  int cells, n, thr;
+};
+int push_waves(const KParams &kp, const PushPlan &pl);
 size_t push_lds_bytes(const KParams &kp, int prec, int cells);
-void launch_push(const KParams &kp, int prec, int cells, const PartPtrs &pp, const void *Est, const void *Bst,
+void launch_push(const KParams &kp, int prec, const PushPlan &pl, const PartPtrs &pp, const void *Est, const void *Bst,
                  uint8_t *dirc, uint16_t *cnt, int32_t *err, int count_moves, void *sink, hipStream_t st);
 // The energy-conserving variant's fixed-point pass: pushes each particle
 // with pp.gbar (gamma(u^n) if null) without touching the state, writes
 // gbar_next = (gamma(u^n) + gamma(u^{n+1}))/2 and raises *chg to the bits of
 // max |gbar_next - gbar| / gbar.
-void launch_gamma_mean(const KParams &kp, int prec, int cells, const PartPtrs &pp, const void *Est,
+void launch_gamma_mean(const KParams &kp, int prec, const PushPlan &pl, const PartPtrs &pp, const void *Est,
                        const void *Bst, int32_t *err, void *sink, void *gbar_next, unsigned long long *chg,
                        hipStream_t st);
 // one secant step per particle of the energy-conserving fixed point
@@ -166,8 +172,8 @@ size_t scan_tmp_elems(int n);
 // 8: a recomputed position further than rounding outside that cell; *clamps
 // += particles within rounding outside it, put on its face).  kep[w] gets
 // the FP64 kinetic energy of the particles wave w pushed (push_waves of them,
-// in the segment order).
-void launch_push_scatter(const KParams &kp, int prec, int cells, const PartPtrs &src, const void *Est,
+// in a fixed order).
+void launch_push_scatter(const KParams &kp, int prec, const PushPlan &pl, const PartPtrs &src, const void *Est,
                          const void *Bst, const uint8_t *dirc, const uint16_t *pre, const int32_t *bin_start_new,
                          const PartPtrs &out, int ntot, int32_t *err, unsigned long long *clamps, int32_t *perm,
                          void *sink, double *kep, hipStream_t st);

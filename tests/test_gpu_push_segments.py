@@ -18,6 +18,12 @@ CASES = {
     "2d_67x65_crowded_rows": (oracle.Grid(dim=2, nx=67, ny=65, dx=1.0, dy=0.9, dt=0.4), 300000, 0.9),
     "2d_203x101_three_species": (oracle.Grid(dim=2, nx=203, ny=101, dx=1.0, dy=1.1, dt=0.4, q=(1.0, -1.0, 2.0),
                                              m=(1.0, 1.0, 3.0)), 700000, 0.0),
+    # crowded segments split over several waves: 2 parts of 2 cells (counting
+    # pass) and 3 (scatter), the 1-cell segments at the rows' ends whole; 5 and
+    # 8 parts of 8 cells
+    "2d_97x89_split_three_species": (oracle.Grid(dim=2, nx=97, ny=89, dx=1.0, dy=1.1, dt=0.4, q=(1.0, -1.0, 2.0),
+                                                 m=(1.0, 1.0, 3.0)), 120000, 0.7),
+    "3d_29x27x23_split": (oracle.Grid(dim=3, nx=29, ny=27, nz=23, dx=1.0, dy=0.9, dz=1.1, dt=0.4), 100000, 0.5),
     "3d_37x35x33": (oracle.Grid(dim=3, nx=37, ny=35, nz=33, dx=1.0, dy=0.9, dz=1.1, dt=0.4), 50000, 0.0),
 }
 
