@@ -577,7 +577,7 @@ int relsim_deposit_moments_ec(relsim_ctx *c, const relsim_particles *pt, const d
   void *stB = c->at<char>(c->L.stB);
   PartPtrs pp = front(pt);
   pp.gbar = gbar;
-  timed(c, "stage_fields", [&] { launch_stage_field(c->kp, c->p.precision, B_n, stB, c->st); });
+  timed(c, "stage_fields", [&] { launch_stage_field(c->kp, c->p.precision, B_n, stB, nullptr, nullptr, nullptr, c->st); });
   timed(c, "deposit_cells", [&] { launch_deposit_cells(c->kp, c->p.precision, G, pp, stB, S, c->st); });
   timed(c, "assemble_nodes", [&] { launch_assemble(c->kp, c->p.precision, c->p.mass_fp32, S, Jhat, M, c->st); });
   return launch_status(c, "relsim_deposit_moments");
@@ -623,8 +623,7 @@ int relsim_push_ec(relsim_ctx *c, relsim_particles *pt, const double *E_theta, c
   void *stB = c->at<char>(c->L.stB);
   void *stE = c->at<char>(c->L.stE);
   timed(c, "stage_fields", [&] {
-    launch_stage_field(c->kp, c->p.precision, B_n, stB, c->st);
-    launch_stage_field(c->kp, c->p.precision, E_theta, stE, c->st);
+    launch_stage_field(c->kp, c->p.precision, B_n, stB, E_theta, stE, nullptr, c->st);
   });
   // with resort the first pass only counts the moves, and the second pushes
   // again, writing the new state straight into its new place
@@ -671,10 +670,8 @@ int relsim_gamma_mean(relsim_ctx *c, const relsim_particles *pt, const double *E
   void *stE = c->at<char>(c->L.stE);
   PartPtrs pp = front(pt);
   pp.gbar = gbar;
-  HIP_CHECK(c, hipMemsetAsync(chg, 0, sizeof(unsigned long long), c->st));
   timed(c, "stage_fields", [&] {
-    launch_stage_field(c->kp, c->p.precision, B_n, stB, c->st);
-    launch_stage_field(c->kp, c->p.precision, E_theta, stE, c->st);
+    launch_stage_field(c->kp, c->p.precision, B_n, stB, E_theta, stE, chg, c->st);
   });
   timed(c, "gamma_mean", [&] {
     launch_gamma_mean(c->kp, c->p.precision, plan, pp, stE, stB, err, c->at<char>(c->L.sink), gbar_next, chg,
