@@ -425,16 +425,35 @@ constexpr int kXcdDeposit = 8;
 // ---------------------------------------------------------------------------
 // 2D: the G lanes of a group split the cell's particles; each lane sums all
 // 93 moments (81 mass, 12 current) of its particles, and the group's G
-// partial sums are then added in fixed lane order.
+// partial sums are then added in fixed lane order.  In FP64 the 93 sums take
+// 186 of the 256 registers that two waves to a SIMD leave, too many beside two
+// records: with the next one in registers a SIMD held one wave, and the
+// compiler's cut to two waves spilled inside the loop (161 us, and 202, for
+// 10.4M particles, 512 per cell).  The next record is therefore loaded straight
+// into LDS and a round reads its own from there: 145 us, 3.4 TB/s.  32 rounds
+// of G stay the best size of a group (16: 151 us, 8: 172).
+// A 2D FP64 record travels from memory to LDS without passing through
+// registers: lane l's three 16-byte pieces (offsets, u_x u_y, u_z w) go to
+// 16 l in the three KiB at dst.
+__device__ __forceinline__ void lds_load_rec(int q, const V2<double> *__restrict__ xy,
+                                             const V4<double> *__restrict__ uw, char *dst) {
+  using GP = const __attribute__((address_space(1))) void *;
+  using LP = __attribute__((address_space(3))) void *;
+  const char *const b = reinterpret_cast<const char *>(uw + q);
+  __builtin_amdgcn_global_load_lds((GP)(xy + q), (LP)dst, 16, 0, 0);
+  __builtin_amdgcn_global_load_lds((GP)b, (LP)(dst + 1024), 16, 0, 0);
+  __builtin_amdgcn_global_load_lds((GP)(b + 16), (LP)(dst + 2048), 16, 0, 0);
+}
+
 template <typename T, int G, bool GB>
-__global__ __launch_bounds__(64) void k_deposit_cells(KParams kp, const int32_t *__restrict__ bin_start,
+__global__ __launch_bounds__(64, sizeof(T) == 8 ? 2 : 1) void k_deposit_cells(KParams kp, const int32_t *__restrict__ bin_start,
                                                       const V2<T> *__restrict__ xy,
                                                       const V4<T> *__restrict__ uw,
                                                       const V4<T> *__restrict__ Bs, T *__restrict__ S,
                                                       const T *__restrict__ gb) {
   constexpr int NACC = 93;  // 81 mass moments + 12 current moments
   constexpr int CH = 32;    // moments per LDS transpose chunk (keeps LDS off the occupancy limit)
-  __shared__ T red[64 * (CH + 1)];
+  __shared__ alignas(16) T red[64 * (CH + 1)];
   __shared__ V4<T> bsh[64 / G][9];
   __shared__ T stab[2][8];
   const int lane = threadIdx.x, grp = lane / G, gl = lane % G;
@@ -453,23 +472,57 @@ __global__ __launch_bounds__(64) void k_deposit_cells(KParams kp, const int32_t 
   for (int k = 0; k < NACC; ++k) acc[k] = T(0);
   PRec<T> cur{}, nxt{};
   int p = pal + gl;
+  // FP64: the accumulators leave no registers for a record in flight, so it
+  // waits in LDS, in one of two buffers that share the reduction's room
+  constexpr bool VIA_LDS = sizeof(T) == 8;
+  char *const recs = reinterpret_cast<char *>(red);
   if (rounds > 0) {
-    load_rec<T, 2>(p, cs.pend, xy, uw, nullptr, cur);
+    if constexpr (VIA_LDS)
+      lds_load_rec(load_index(p, cs.pend), xy, uw, recs);
+    else
+      load_rec<T, 2>(p, cs.pend, xy, uw, nullptr, cur);
     load_gbar<GB>(p, cs.pend, gb, cur);
   }
   __builtin_amdgcn_s_waitcnt(0);
-#pragma unroll 2
+#pragma unroll (VIA_LDS ? 1 : 2)
   for (int r = 0; r < rounds; ++r) {
     const int pn = p + G;
-    load_rec<T, 2>(pn, cs.pend, xy, uw, nullptr, nxt);
+    if constexpr (VIA_LDS) {
+      // this round's record has landed and the last round's has been read:
+      // the next one may overwrite it
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_s_waitcnt(0);
+      asm volatile("" ::: "memory");
+      const char *const own = recs + 3072 * (r & 1) + 16 * lane;
+      const V2<T> o = *reinterpret_cast<const V2<T> *>(own), b0 = *reinterpret_cast<const V2<T> *>(own + 1024),
+                  b1 = *reinterpret_cast<const V2<T> *>(own + 2048);
+      cur.fx = o.x;
+      cur.fy = o.y;
+      cur.ux = b0.x;
+      cur.uy = b0.y;
+      cur.uz = b1.x;
+      cur.w = b1.y;
+    } else {
+      load_rec<T, 2>(pn, cs.pend, xy, uw, nullptr, nxt);
+    }
     load_gbar<GB>(pn, cs.pend, gb, nxt);
+    T qs, bs, Bx, By, Bz;
+    auto from_lds = [&] {
+      species_of<T>(kp, pc, cs, p, stab, qs, bs);
+      gather_B<T, 2>(bsh[grp] + 4, 3, 9, cur.fx, cur.fy, T(0), Bx, By, Bz);
+    };
+    if constexpr (VIA_LDS) {
+      // every lane reads LDS before the next record is asked for: a read
+      // after that would wait for it
+      from_lds();
+      __builtin_amdgcn_sched_barrier(0);
+      lds_load_rec(load_index(pn, cs.pend), xy, uw, recs + 3072 * ((r + 1) & 1));
+      __builtin_amdgcn_sched_barrier(0);
+    }
     if (p >= cs.pbeg && p < cs.pend) {
       const T fx = cur.fx, fy = cur.fy;
       const T ux = cur.ux, uy = cur.uy, uz = cur.uz, wp = cur.w;
-      T qs, bs;
-      species_of<T>(kp, pc, cs, p, stab, qs, bs);
-      T Bx, By, Bz;
-      gather_B<T, 2>(bsh[grp] + 4, 3, 9, fx, fy, T(0), Bx, By, Bz);
+      if constexpr (!VIA_LDS) from_lds();
       const T igb = inv_gbar<GB>(kp, pc, cur, ux, uy, uz);
       const T kb = bs * igb * pc.invc;
       T a[9];
@@ -498,8 +551,17 @@ __global__ __launch_bounds__(64) void k_deposit_cells(KParams kp, const int32_t 
         for (int k = 0; k < 3; ++k) acc[81 + cxy * 3 + k] += wgt * psiJ[k];
       }
     }
-    cur = nxt;
+    if constexpr (VIA_LDS)
+      cur.g = nxt.g;
+    else
+      cur = nxt;
     p = pn;
+  }
+  if constexpr (VIA_LDS) {
+    // the last record asked for has landed: the reduction may use its room
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
   }
   // group reduction, CH moments at a time: registers -> LDS transpose ->
   // G-term sums in fixed lane order
