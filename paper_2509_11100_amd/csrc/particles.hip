@@ -606,8 +606,13 @@ __global__ __launch_bounds__(64) void k_deposit_split3(KParams kp, const int32_t
                                                        const T *__restrict__ gb) {
   constexpr int G = 4;
   // per producing lane: operand blocks (X0 X1 X2 Y0) (Y1 Y2 P0 P1) (P2..P5)
-  // (P6 P7 P8 -) for the mass lanes [0] and the current lane [1], and Z
-  __shared__ V4<T> sh[2][4][64];
+  // (P6 P7 P8 -) for the mass lanes and, but for the last, the current lane
+  // (whose sums with P6 to P8 are not stored), and Z (1 for the current lane).
+  // Without a block of zeros for that lane and its Z written each round: 627 ->
+  // 612 us with the assembly on 128 x 64 x 64, 16 per cell, 3871 -> 3795 on 256
+  // x 128 x 128 (M in FP32).  Z in the blocks' spare words (12.4 KB instead of
+  // 13.4, 12 waves per CU instead of 11): the same.
+  __shared__ V4<T> sh[7][64];
   __shared__ T zsh[4][64];
   __shared__ P3<T> bsh[64 / G][27];
   __shared__ T stab[2][8];
@@ -626,7 +631,8 @@ __global__ __launch_bounds__(64) void k_deposit_split3(KParams kp, const int32_t
   fill_species_table<T>(pc, stab, lane);
   __syncthreads();
   const bool isJ = gl == 3;
-  const V4<T> *const mine = &sh[isJ ? 1 : 0][0][0];
+  const V4<T> *const mine = sh[isJ ? 4 : 0];
+  zsh[3][lane] = T(1);
 
   T acc[81];
 #pragma unroll
@@ -668,7 +674,7 @@ __global__ __launch_bounds__(64) void k_deposit_split3(KParams kp, const int32_t
       const T j1 = cJ * (a[3] * ux + a[4] * uy + a[5] * uz);
       const T j2 = cJ * (a[6] * ux + a[7] * uy + a[8] * uz);
       const T nx0 = T(1) - fx, ny0 = T(1) - fy, nz0 = T(1) - fz;
-      V4<T> m0, m1, m2, m3, c0, c1, c2, c3;
+      V4<T> m0, m1, m2, m3, c0, c1, c2;
       m0.x = nx0 * nx0;
       m0.y = nx0 * fx;
       m0.z = fx * fx;
@@ -697,29 +703,23 @@ __global__ __launch_bounds__(64) void k_deposit_split3(KParams kp, const int32_t
       c2.y = j0 * fz;
       c2.z = j1 * fz;
       c2.w = j2 * fz;
-      c3.x = T(0);
-      c3.y = T(0);
-      c3.z = T(0);
-      c3.w = T(0);
       __syncthreads();  // the previous round's reads are done
-      sh[0][0][lane] = m0;
-      sh[0][1][lane] = m1;
-      sh[0][2][lane] = m2;
-      sh[0][3][lane] = m3;
-      sh[1][0][lane] = c0;
-      sh[1][1][lane] = c1;
-      sh[1][2][lane] = c2;
-      sh[1][3][lane] = c3;
+      sh[0][lane] = m0;
+      sh[1][lane] = m1;
+      sh[2][lane] = m2;
+      sh[3][lane] = m3;
+      sh[4][lane] = c0;
+      sh[5][lane] = c1;
+      sh[6][lane] = c2;
       zsh[0][lane] = nz0 * nz0;
       zsh[1][lane] = nz0 * fz;
       zsh[2][lane] = fz * fz;
-      zsh[3][lane] = T(1);
       __syncthreads();
     }
 #pragma unroll 1
     for (int j = 0; j < G; ++j) {
       const int src = grp * G + j;
-      const V4<T> v0 = mine[src], v1 = mine[64 + src], v2 = mine[128 + src], v3 = mine[192 + src];
+      const V4<T> v0 = mine[src], v1 = mine[64 + src], v2 = mine[128 + src], v3 = sh[3][src];
       const T Z = zsh[gl][src];
       const T XZ[3] = {v0.x * Z, v0.y * Z, v0.z * Z};
       const T Y[3] = {v0.w, v1.x, v1.y};
