@@ -156,8 +156,8 @@ int relsim_deposit_moments(relsim_ctx *ctx, const relsim_particles *part, const 
 /* a5 (S4-S5): restarted GMRES for E_th from the initial guess E^n, then the
  * field update.  E_theta, E_np1, B_np1 are written.  iters / rel_resid (host
  * pointers, may be NULL) receive the Arnoldi steps taken and the final true
- * relative residual.  Synchronous (one small device-to-host copy per Arnoldi
- * step).  Returns RELSIM_ENOTCONVERGED with the last iterate written when
+ * relative residual.  Synchronous (one wait for a small copy of the
+ * solver's state).  Returns RELSIM_ENOTCONVERGED with the last iterate written when
  * gmres_maxit is reached. */
 int relsim_field_solve(relsim_ctx *ctx, const void *M, const double *Jhat, const double *E_n, const double *B_n,
                        double *E_theta, double *E_np1, double *B_np1, int32_t *iters, double *rel_resid);
