@@ -118,9 +118,10 @@ __device__ __forceinline__ void get_sums(const double *__restrict__ P, int npart
 
 // Whether the kernels of column j have nothing to do: the solve has ended,
 // or its cycle ended with an earlier column.  A block that starts after block
-// 0 of its own kernel has recorded an end would come to the same end.  One
-// thread of a block reads the state for all of it, so that the block stays
-// together.
+// 0 of its own kernel has recorded an end would come to the same end, and one
+// that started before decides from entries that block 0 leaves alone in that
+// kernel.  One thread of a block reads the state for all of it, so that the
+// block stays together.
 __device__ __forceinline__ bool arnoldi_off(const GmState *st, int j) {
   return st->code != 0 || st->done != 0 || (st->end_at >= 0 && st->end_at < j);
 }
@@ -603,11 +604,12 @@ __global__ __launch_bounds__(TB) void k_gm_adj_start(KParams kp, GmBuf gm, const
 }
 
 // The cycle ends with column k, whose vector's norm is hn: its last rotation.
-// One thread.
+// One thread.  Blocks of the same kernel may still read a and g[k] to come to
+// the same end, so the rotated entry of row k goes into a place of its own.
 __device__ __forceinline__ void end_cycle(GmState *st, int k, double hn) {
   const double a = st->a, den = hypot(a, hn);
   st->R[(size_t)k * (kMaxRestart + 1) + k] = den;
-  st->g[k] *= den > 0 ? a / den : 1.0;
+  st->g_end = st->g[k] * (den > 0 ? a / den : 1.0);
   st->end_at = k;
 }
 
@@ -641,8 +643,10 @@ __global__ __launch_bounds__(kOpThreads<DIM>, DIM == 3 ? NW3 / 4 : (NV <= 32 ? 2
     const int code = (cycle0 && !isfinite(bnorm)) ? kGmBadRhs : (!isfinite(wn) ? kGmBadResidual : 0);
     const bool conv = cycle0 && wn <= tol;
     if (head) {
-      st->bnorm = bnorm;
-      st->tol = tol;
+      if (cycle0) {  // later cycles read bnorm here
+        st->bnorm = bnorm;
+        st->tol = tol;
+      }
       st->rel = bnorm > 0 ? wn / bnorm : 0.0;
       st->g[0] = wn;
       st->wn = wn;
@@ -860,7 +864,7 @@ __global__ __launch_bounds__(TB) void k_gm_update(GmBuf gm, double *__restrict__
   const int n = st->end_at + 1;
   if (threadIdx.x < 64) {
     const int lane = threadIdx.x;  // n <= 64: one row per lane
-    double g = lane < n ? st->g[lane] : 0.0;
+    double g = lane < n - 1 ? st->g[lane] : (lane == n - 1 ? st->g_end : 0.0);
     for (int k = n - 1; k >= 0; --k) {
       const double *const col = st->R + (size_t)k * (kMaxRestart + 1);
       const double d = col[k], gk = __shfl(g, k);

@@ -223,6 +223,7 @@ struct GmState : GmHead {
   double wn;                                   // norm of the column's candidate vector
   double a;                                    // last rotated entry of the newest column
   double g[kMaxRestart + 1];                   // the rotated right-hand side
+  double g_end;                                // row end_at of it, after the cycle's last rotation
   double cs[kMaxRestart], sn[kMaxRestart];     // the rotations
   // the Hessenberg matrix and its rotated form, column k at k (kMaxRestart + 1)
   double H[kMaxRestart * (kMaxRestart + 1)], R[kMaxRestart * (kMaxRestart + 1)];
