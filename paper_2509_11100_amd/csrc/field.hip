@@ -9,7 +9,7 @@ template <int DIM>
 __global__ __launch_bounds__(256) void k_curl(KParams kp, const double *__restrict__ in, double *__restrict__ out,
                                               int shift) {
   int i, j, k;
-  const int g = strip_node(kp.nx, kp.ny, kp.nz, xcd_remap(blockIdx.x, gridDim.x) * 4 + (int)(threadIdx.x >> 6),
+  const int g = strip_node(kp.nx, kp.ny, kp.nz, xcd_bands(blockIdx.x, gridDim.x) * 4 + (int)(threadIdx.x >> 6),
                            (int)(threadIdx.x & 63), i, j, k);
   if (g < 0) return;
   double c[3][8], r[3];

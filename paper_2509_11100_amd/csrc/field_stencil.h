@@ -8,18 +8,13 @@
 // transpose of C_NC on the periodic grid.
 #pragma once
 
+#include "block_order.h"
 #include "relsim_internal.h"
 
 namespace relsim {
 namespace {
 
 __device__ __forceinline__ int wrapi(int i, int n) { return i < 0 ? i + n : (i >= n ? i - n : i); }
-
-__device__ __forceinline__ int xcd_remap(int b, int nb) {
-  const int q = nb >> 3;
-  if (b >= (q << 3)) return b;
-  return (b & 7) * q + (b >> 3);
-}
 
 // Cube of 2^DIM values of the three components starting at (i0, j0, k0).
 template <int DIM>

@@ -50,7 +50,7 @@ struct Groups {
 __device__ __forceinline__ Groups block_groups(int ng) {
   const int nb = (int)gridDim.x, b = (int)blockIdx.x;
   if (nb == ng) {
-    const int first = xcd_remap(b, nb);
+    const int first = xcd_bands(b, nb);
     return {first, first + 1, 1};
   }
   if (nb & 7) return {b, ng, nb};

@@ -15,8 +15,8 @@
 // and segments are visited tile by tile (2D tiles of up to 16 x 8 cells, 3D
 // of up to 16 x 4 x 4), so that neighbouring cells, whose particles exchange
 // places in the re-sort, are processed close together in time; workgroups
-// are remapped so that each XCD (and its L2) works on one contiguous band.
-// The next rounds' particle loads are issued before the current round is
+// are remapped so that an XCD (and its L2) works on neighbouring cells, one
+// band of the grid or a chunk at a time (block_order.h).  The next rounds' particle loads are issued before the current round is
 // computed.
 //
 // Deposit formulation.  For a particle with in-cell offsets f_d, the CIC
@@ -35,29 +35,11 @@
 // M_{g,g'} == M_{g',g} bit for bit.
 #include <climits>
 
+#include "block_order.h"
 #include "relsim_internal.h"
 
 namespace relsim {
 namespace {
-
-// Consecutive workgroups are dispatched to the 8 XCDs round robin.  Remapped
-// so that an XCD (and its L2) works through chunks of `chunk` consecutive
-// work items, the chunks going round the XCDs: neighbouring items share an
-// L2, and a band of the grid that holds more particles than the rest is
-// spread over all XCDs.  Items past the last whole round of chunks keep their
-// place.
-__device__ __forceinline__ int xcd_chunk(int b, int nb, int chunk) {
-  const int round = chunk << 3;
-  if (b >= nb / round * round) return b;
-  const int i = b >> 3, c = i / chunk;
-  return (c * 8 + (b & 7)) * chunk + (i - c * chunk);
-}
-
-__device__ __forceinline__ int xcd_remap(int b, int nb) {
-  const int q = nb >> 3;
-  if (b >= (q << 3)) return b;
-  return (b & 7) * q + (b >> 3);
-}
 
 __device__ __forceinline__ int wrapi(int i, int n) { return i < 0 ? i + n : (i >= n ? i - n : i); }
 
@@ -415,11 +397,6 @@ __device__ __forceinline__ T inv_gbar(const KParams &kp, const PC<T> &pc, const 
     return kp.nonrel ? T(1) : rsqrt_t(T(1) + (ux * ux + uy * uy + uz * uz) * pc.invc2);
 }
 
-// An XCD takes 512 cells (4 tiles) at a time in the 2D deposit: 8 G blocks of
-// 64 / G cells.  One band per XCD leaves most of the particles of a sheet to
-// two XCDs (625 x 625 reconnection sheet: 282 -> 263 us mixed, 515 -> 467 us
-// FP64; evenly filled sheets unchanged; 2048 cells at a time 316 us).
-constexpr int kXcdDeposit = 8;
 // ---------------------------------------------------------------------------
 // S1-S3: per-cell moments
 // ---------------------------------------------------------------------------
@@ -457,7 +434,7 @@ __global__ __launch_bounds__(64, sizeof(T) == 8 ? 2 : 1) void k_deposit_cells(KP
   __shared__ V4<T> bsh[64 / G][9];
   __shared__ T stab[2][8];
   const int lane = threadIdx.x, grp = lane / G, gl = lane % G;
-  const int blk = xcd_chunk(blockIdx.x, gridDim.x, kXcdDeposit * G);
+  const int blk = deposit_block(blockIdx.x, gridDim.x, G, kp.ncells);
   const CellSpan cs = slot_span<G>(kp, bin_start, blk, grp);
   const PC<T> pc(kp);
 
@@ -763,7 +740,7 @@ __global__ __launch_bounds__(256) void k_assemble(KParams kp, const T *__restric
                                                   MT *__restrict__ M) {
   constexpr int NSLOT = m_slots<DIM>(), CEN = m_centre<DIM>();
   constexpr int NCORN = DIM == 3 ? 8 : 4;
-  const int blk = xcd_remap(blockIdx.x, gridDim.x);
+  const int blk = xcd_bands(blockIdx.x, gridDim.x);
   const int g = blk * blockDim.x + threadIdx.x;
   if (g >= kp.ncells) return;
   const size_t N = (size_t)kp.ncells;
@@ -1136,7 +1113,7 @@ __device__ __forceinline__ int segment_holding(const KParams &kp, int C, int nse
 __device__ __forceinline__ WavePart wave_work(const KParams &kp, const SegTiles &tl,
                                               const int32_t *__restrict__ bin_start, int lane) {
   const int b = (int)blockIdx.x;
-  if (b >= tl.ns) return {xcd_chunk(b - tl.ns, (int)gridDim.x - tl.ns, tl.chunk), 0};
+  if (b >= tl.ns) return {xcd_chunks(b - tl.ns, (int)gridDim.x - tl.ns, tl.chunk), 0};
   const int p = b * tl.thr;
   const int z = __builtin_amdgcn_readfirstlane(segment_holding(kp, tl.C, tl.nseg, p, bin_start, lane));
   const int row = z / tl.nseg, s = z - row * tl.nseg, i0 = s * tl.C, cells = min(tl.C, kp.nx - i0);
@@ -1601,7 +1578,7 @@ __global__ __launch_bounds__(64) void k_kinetic(KParams kp, const int32_t *__res
   // one block per 64/G cells in slot order; block b writes partials[b]
   __shared__ double red[64];
   const int lane = threadIdx.x, grp = lane / G, gl = lane % G;
-  const int blk = xcd_remap(blockIdx.x, gridDim.x);
+  const int blk = xcd_bands(blockIdx.x, gridDim.x);
   const CellSpan cs = slot_span<G>(kp, bin_start, blk, grp);
   const double invc2 = kp.inv_c2;
   const int S = kp.nspecies;
