@@ -136,19 +136,20 @@ struct PC<double> {
 
 
 // Ghosted copies of SoA FP64 grid fields (one thread per ghosted point): F0,
-// and in the second row of blocks F1.  *clear, when given, is set to zero: a
-// copy of 20 thousand points takes 4 us, nearly all of it the launch, so the
-// push passes stage both fields, and the fixed-point pass also clears its
-// maximum, in the one launch.  Fixed-point pass on 200 x 102 cells, 10.4M
+// and with TWO in the second row of blocks F1, and *clear, when given, is set
+// to zero: a copy of 20 thousand points takes 4 us, nearly all of it the launch,
+// so the push passes stage both fields, and the fixed-point pass also clears
+// its maximum, in the one launch.  Fixed-point pass on 200 x 102 cells, 10.4M
 // particles: 195 -> 188 us (a push with re-sort, which nobody waits for, takes
-// 37 us on 64 x 32 cells either way).
-template <typename T, int DIM>
+// 37 us on 64 x 32 cells either way).  The deposit stages one field, and does
+// not choose: 2.8 -> 2.6 us on 64 x 32 cells, 5.1 -> 4.6 on 100 x 77.
+template <typename T, int DIM, bool TWO>
 __global__ __launch_bounds__(256) void k_stage_field(KParams kp, const double *__restrict__ F0, V4<T> *__restrict__ out0,
                                                      const double *__restrict__ F1, V4<T> *__restrict__ out1,
                                                      unsigned long long *__restrict__ clear) {
-  const double *__restrict__ F = blockIdx.y ? F1 : F0;
-  V4<T> *__restrict__ out = blockIdx.y ? out1 : out0;
-  if (clear && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *clear = 0;
+  const double *__restrict__ F = TWO && blockIdx.y ? F1 : F0;
+  V4<T> *__restrict__ out = TWO && blockIdx.y ? out1 : out0;
+  if (TWO && clear && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *clear = 0;
   const int g = blockIdx.x * 256 + threadIdx.x;
   if (g >= kp.nghost) return;
   const int gi = g % kp.gx, gj = (g / kp.gx) % (kp.ny + 2);
@@ -1814,10 +1815,16 @@ struct KineticF {
 
 void launch_stage_field(const KParams &kp, int prec, const double *F0, void *out0, const double *F1, void *out1,
                         unsigned long long *clear, hipStream_t st) {
-  const dim3 grid((kp.nghost + 255) / 256, F1 ? 2 : 1);
-#define RELSIM_STAGE(T, DIM)                                                                                   \
-  hipLaunchKernelGGL((k_stage_field<T, DIM>), grid, dim3(256), 0, st, kp, F0, mp<V4<T>>(out0), F1, mp<V4<T>>(out1), \
-                     clear)
+  const int nblk = (kp.nghost + 255) / 256;
+#define RELSIM_STAGE(T, DIM)                                                                                           \
+  do {                                                                                                                 \
+    if (F1)                                                                                                            \
+      hipLaunchKernelGGL((k_stage_field<T, DIM, true>), dim3(nblk, 2), dim3(256), 0, st, kp, F0, mp<V4<T>>(out0), F1,  \
+                         mp<V4<T>>(out1), clear);                                                                      \
+    else                                                                                                               \
+      hipLaunchKernelGGL((k_stage_field<T, DIM, false>), dim3(nblk), dim3(256), 0, st, kp, F0, mp<V4<T>>(out0), F1,    \
+                         mp<V4<T>>(out1), clear);                                                                      \
+  } while (0)
   if (prec == RELSIM_MIXED) {
     if (kp.dim == 2)
       RELSIM_STAGE(float, 2);

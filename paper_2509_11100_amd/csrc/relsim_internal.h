@@ -132,7 +132,7 @@ struct PartPtrs {
 // Ghosted, component-interleaved copy of a grid vector field (SoA FP64 on
 // nodes or centres) in the particle arithmetic type: point (i, j, k) with
 // i in [-1, nx], ... at (i + 1) + gx (j + 1) [+ gxy (k + 1)], 4 values each.
-// (F1 may be null; *clear, when given, is zeroed)
+// (F1 may be null; *clear, when given with F1, is zeroed)
 void launch_stage_field(const KParams &kp, int prec, const double *F0, void *out0, const double *F1, void *out1,
                         unsigned long long *clear, hipStream_t st);
 void launch_deposit_cells(const KParams &kp, int prec, int group, const PartPtrs &pp, const void *Bst, void *S,
