@@ -341,7 +341,15 @@ PushPlan plan_push(const relsim_ctx *c, int64_t n, KernelKind k) {
 // grids.  The 2D deposit amortises its per-cell reduction over many rounds
 // (16 in FP32; 32 in FP64, whose register-bound occupancy favours narrower
 // groups) and may go down to 4 lanes.  (The 3D deposit always splits a
-// cell's moments over 4 lanes and takes no group.)
+// cell's moments over 4 lanes and takes no group.)  4 FP64 lanes take a crowded
+// cell's particles one after another, and the few such cells' waves are all that
+// runs in the end; the launch then gets 8 where it has few waves, or where more
+// than two species say that some of them fill a part of the grid only (the
+// sheet's own, in crowded rows): us with 4 and 8, reconnection sheet of 256 x
+// 256 cells, 56 per cell on average, 191 and 124, 300 x 300, 98 per cell, 368 and
+// 236, 440 x 440 303 and 254; evenly filled, 256 x 256 cells with 32 and 64 per
+// cell 63.7 and 63.9, 91.6 and 88.2, 512 x 256 with 64 176 and 180, 320 x 310
+// with 32 92 and 99 (which keeps 4).
 int choose_group(const relsim_params &p, const KParams &kp, int64_t n, KernelKind k = K_OTHER) {
   if (p.group) return p.group;
   const bool fp64 = p.precision == RELSIM_FP64;
@@ -351,6 +359,8 @@ int choose_group(const relsim_params &p, const KParams &kp, int64_t n, KernelKin
   int g = k == K_DEPOSIT ? 4 : 8;
   while (g < 64 && 2.0 * g <= mean / rounds) g *= 2;
   while (g < 64 && (double)kp.ncells * g < 512.0 * 64.0) g *= 2;
+  const double waves = (double)kp.ncells * g / 64.0;
+  if (k == K_DEPOSIT && fp64 && g == 4 && mean >= 24.0 && waves < (p.nspecies > 2 ? 12288.0 : 4097.0)) g = 8;
   return g;
 }
 
