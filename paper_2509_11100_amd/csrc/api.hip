@@ -158,32 +158,41 @@ constexpr int kMostBlocks = std::max(kGmNodeBlocks, kGmTileBlocks);
 // Stride of the Krylov basis's rows: even, for 16-byte access.
 size_t gm_stride(size_t n3) { return (n3 + 1) & ~(size_t)1; }
 
-// Rows of the push passes' tiles (about 16 cells wide): 32 in 2D, 16 in 3D,
-// fewer where a tile's particles take more than 512 KiB.  An XCD works on
-// several tiles at a time, and their particles and destinations share its 4
-// MiB of L2 (200 x 102 sheet, 512 FP64 particles per cell: 380 us with 34
-// rows, 376 up to 1 to 4 MiB, 371 up to 512 KiB; 317 x 211, 80 per cell: 163
-// -> 159 us; the sheets below keep their times).
-int push_tile_rows(const relsim_params *p) {
-  const double nc = (double)p->nx * p->ny * (p->dim == 3 ? p->nz : 1);
-  const double row = 16.0 * (p->dim == 3 ? 4 : 1) * (double)p->max_particles / nc *
-                     (p->dim == 3 ? 8 : 6) * (p->precision == RELSIM_MIXED ? 4 : 8);
-  int rows = p->dim == 3 ? 16 : 32;
-  while (rows > 1 && rows * row > (double)(1 << 19)) rows /= 2;
-  return rows;
+// Rows and layers of the push passes' tiles: 32 rows in 2D, 16 rows of 4
+// layers in 3D, first fewer layers and then fewer rows where the particles of
+// 16 cells' width take more than 512 KiB.  An XCD works on several tiles at a
+// time, and their particles and destinations share its 4 MiB of L2 (200 x 102
+// sheet, 512 FP64 particles per cell: 380 us with 34 rows, 376 up to 1 to 4 MiB,
+// 371 up to 512 KiB; 317 x 211, 80 per cell: 163 -> 159 us; 72 x 60 x 50 FP64,
+// 32 per cell: 446, 448 and 458 us with 16 rows of 1, 2 and 4 layers, 450, 459
+// and 475 with 8; 256 x 128 x 128 mixed, 16 per cell: 2550, 2520 and 2513, and
+// 2548, 2582 and 2563).
+struct PushTile {
+  int rows, layers;
+};
+PushTile push_tile(const relsim_params *p) {
+  const bool three = p->dim == 3;
+  const double nc = (double)p->nx * p->ny * (three ? p->nz : 1);
+  const double row = 16.0 * (double)p->max_particles / nc * (three ? 8 : 6) * (p->precision == RELSIM_MIXED ? 4 : 8);
+  int rows = three ? 16 : 32, layers = three ? 4 : 1;
+  auto over = [&] { return rows * layers * row > (double)(1 << 19); };
+  while (layers > 1 && over()) layers /= 2;
+  while (rows > 1 && over()) rows /= 2;
+  // equal tiles, a quarter higher or deeper at most
+  return {even_tile(p->ny, rows, rows + rows / 4), three ? even_tile(p->nz, layers, layers + layers / 4) : 1};
 }
 
 // Most waves of a push pass: segments of one cell, in the tiles that
 // make_kparams and the push passes choose.
 size_t max_push_waves(const relsim_params *p) {
-  auto padded = [](int n, int cap) {
-    const int t = even_tile(n, cap);
-    return (size_t)((n + t - 1) / t) * t;
-  };
+  auto padded = [](int n, int t) { return (size_t)((n + t - 1) / t) * t; };
+  const PushTile t = push_tile(p);
   size_t most = 0;
-  for (int C = 1; C <= 64; C *= 2)  // segments side by side in a tile: 16 / C
-    most = std::max(most, padded((p->nx + C - 1) / C, C < 16 ? 16 / C : 1));
-  return most * padded(p->ny, push_tile_rows(p)) * (p->dim == 3 ? padded(p->nz, 4) : 1) + kMaxSplits;
+  for (int C = 1; C <= 64; C *= 2) {
+    const int nseg = (p->nx + C - 1) / C;
+    most = std::max(most, padded(nseg, tile_segments(p->dim, nseg, C)));
+  }
+  return most * padded(p->ny, t.rows) * (p->dim == 3 ? padded(p->nz, t.layers) : 1) + kMaxSplits;
 }
 
 Layout make_layout(const relsim_params *p) {
@@ -253,15 +262,15 @@ KParams make_kparams(const relsim_params *p) {
   k.tx = tile(k.nx, 16);
   k.ty = tile(k.ny, p->dim == 3 ? 4 : 8);
   k.tz = p->dim == 3 ? tile(k.nz, 4) : 1;
-  // the push passes visit their row segments in taller tiles (2D 32 rows,
-  // 3D 16 rows x 4 layers): the re-sort then writes each destination bin's
+  // the push passes visit their row segments in taller tiles: the re-sort then writes each destination bin's
   // runs from the rows above and below it closer together in time, so more
   // of its partly written lines are completed in L2 before they go to HBM
   // (measured against 8 to 512 rows: 5-6 % off the scatter on both grids).
   // Extents that the height does not divide are cut into equal tiles of
   // about that height, the last of which may reach past the grid.
-  k.sty = even_tile(k.ny, push_tile_rows(p));
-  k.stz = p->dim == 3 ? even_tile(k.nz, 4) : 1;
+  const PushTile pt = push_tile(p);
+  k.sty = pt.rows;
+  k.stz = pt.layers;
   auto lg = [](int v) {
     int l = 0;
     while ((1 << l) < v) ++l;

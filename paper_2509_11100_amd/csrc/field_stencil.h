@@ -8,7 +8,6 @@
 // transpose of C_NC on the periodic grid.
 #pragma once
 
-#include "block_order.h"
 #include "relsim_internal.h"
 
 namespace relsim {

@@ -35,7 +35,6 @@
 // M_{g,g'} == M_{g',g} bit for bit.
 #include <climits>
 
-#include "block_order.h"
 #include "relsim_internal.h"
 
 namespace relsim {
@@ -971,7 +970,7 @@ SegTiles seg_tiles(const KParams &kp, const PushPlan &pl) {
   SegTiles t;
   t.C = pl.cells;
   t.nseg = (kp.nx + t.C - 1) / t.C;
-  t.spr = even_tile(t.nseg, t.C < 16 ? 16 / t.C : 1);
+  t.spr = tile_segments(kp.dim, t.nseg, t.C);
   t.ntx = (t.nseg + t.spr - 1) / t.spr;
   t.nty = (kp.ny + kp.sty - 1) / kp.sty;
   t.ntz = (kp.nz + kp.stz - 1) / kp.stz;

@@ -7,6 +7,7 @@
 #include <string>
 #include <vector>
 
+#include "block_order.h"
 #include "relsim.h"
 
 namespace relsim {
@@ -46,14 +47,6 @@ constexpr int kSinkSlots = 512;     // per-lane store sinks of the particle kern
 // Moments per cell: 2D 81 mass moments + 12 current moments; 3D 3 x 81 mass
 // moments (one set per z-monomial type) plus 2 x 12 current moments.
 inline int n_cell_moments(int dim) { return dim == 3 ? 3 * 81 + 2 * 12 : 81 + 12; }
-
-// Extent of equal tiles of about `cap` that cover n places: n / cap rounded
-// down or up tiles, whichever reaches less far past n.
-__host__ __device__ inline int even_tile(int n, int cap) {
-  const int hi = (n + cap - 1) / cap, lo = n / cap > 0 ? n / cap : 1;
-  const int eh = (n + hi - 1) / hi, el = (n + lo - 1) / lo;
-  return el * lo < eh * hi ? el : eh;
-}
 
 // Per-cell moments in memory (93 per cell in 2D, 267 in 3D): blocks of 64
 // consecutive cells, each block holding its moments as 64-cell rows, moment
