@@ -329,17 +329,28 @@ enum KernelKind { K_DEPOSIT, K_PUSH, K_SCATTER, K_OTHER };
 // 745 us (8 and 8: 945, 16 and 4: 860; 450 with the order and the splitting of
 // crowded segments in particles.hip), and on 91 x 47 x 33 cells from 658 to
 // 274 us.
+// A width is not doubled where the row would then reach a quarter further past
+// its end (24 cells: segments of 8, 8 and 8, not 16 and 8: 104 -> 98 us on 24 x
+// 60 x 50).
 PushPlan plan_push(const relsim_ctx *c, int64_t n, KernelKind k) {
   const double rounds = k == K_SCATTER ? 4.0 : 8.0;
   const size_t lds = 8192;
+  const int nx = c->kp.nx;
   const double mean = (double)n / (double)c->kp.ncells;
+  auto reach = [&](int C) { return (nx + C - 1) / C * C; };
   int C = 1;
-  while (C < 64 && 2.0 * C * mean <= rounds * 64.0 && 2 * C <= c->kp.nx && c->kp.ncells / (2 * C) >= 2048 &&
-         push_lds_bytes(c->kp, c->p.precision, 2 * C) <= lds)
+  while (C < 64 && 2.0 * C * mean <= rounds * 64.0 && 2 * C <= nx && c->kp.ncells / (2 * C) >= 2048 &&
+         4 * reach(2 * C) <= 5 * reach(C) && push_lds_bytes(c->kp, c->p.precision, 2 * C) <= lds)
     C *= 2;
-  // a segment is crowded beyond twice the particles aimed at; one of a single
-  // cell is not split
-  const int64_t thr = std::max<int64_t>((int64_t)(2 * 64 * rounds), (n + kMaxSplits - 1) / kMaxSplits);
+  // A segment is crowded beyond twice the particles aimed at; one of a single
+  // cell is not split.  The waves that look for crowded segments are then up to
+  // half as many as the segments, which costs 3 % of a push with re-sort on
+  // evenly filled 3D grids (128 x 31 x 63 FP64 343 -> 335 us without, 96 x 47 x
+  // 33 333 -> 325, 40 x 96 x 96 mixed 420 -> 411).  In 3D, where the segments are
+  // many and the LDS keeps them short, one is crowded from 16 times the mean on.
+  const double most = c->p.dim == 3 ? 16.0 * C * mean : 0.0;
+  const int64_t thr = std::max(std::max<int64_t>((int64_t)(2 * 64 * rounds), (n + kMaxSplits - 1) / kMaxSplits),
+                               (int64_t)most);
   return {C, (int)n, C > 1 ? (int)thr : INT_MAX};
 }
 
