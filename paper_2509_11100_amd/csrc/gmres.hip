@@ -19,8 +19,9 @@
 // A V s lies in the span of v_0 .. v_j, so the next candidate needs no other
 // vector; the Hessenberg column is (z - H s) / nu, and the column before gets
 // the second pass's correction s |w|.  Each step reads the basis twice and
-// takes two kernels (three in 3D, where the curl of the vector is formed
-// first), where two plain passes read it three times in three kernels.
+// takes two kernels (a third, k_gm_dots, has the sums of columns past the 16th
+// in 2D and the 8th in 3D), where two plain passes read it three times in three
+// kernels.
 //
 // Each kernel starts by summing the block partial sums that the one before
 // it left: a dependent kernel costs 2.6 us on this device, a separate
@@ -618,12 +619,13 @@ __device__ __forceinline__ void end_cycle(GmState *st, int k, double hn) {
 constexpr int kQ = 4;
 
 // First half of column j: u = A w~ into V[j + 1], w~ = w / |w| with w in
-// V[j], and the partial sums of w~.u, V^T w~ and V^T u.  The norm of w, summed
-// here, first tells whether column j - 1 was the cycle's last (its residual
-// is |g| |w| / hypot(a, |w|)).  FIRST (j = 0): w is the residual r, whose norm
-// (and in the solve's first cycle the right-hand side's) is summed here.
+// V[j], and the partial sums of w~.u, and with NV (at least j) also of V^T w~
+// and V^T u.  The norm of w, summed here, first tells whether column j - 1 was
+// the cycle's last (its residual is |g| |w| / hypot(a, |w|)).  FIRST (j = 0): w
+// is the residual r, whose norm (and in the solve's first cycle the right-hand
+// side's) is summed here.
 template <int DIM, bool TR, typename MT, int NV, bool FIRST>
-__global__ __launch_bounds__(kOpThreads<DIM>, DIM == 3 ? NW3 / 4 : (NV <= 32 ? 2 : 1)) void k_gm_apply(
+__global__ __launch_bounds__(kOpThreads<DIM>, DIM == 3 ? NW3 / 4 : 2) void k_gm_apply(
     KParams kp, GmBuf gm, const MT *__restrict__ M, int j, int cycle0) {
   constexpr int NW = kOpWaves<DIM>;
   __shared__ double lds[NW * (2 * NV + 1)];
@@ -691,7 +693,7 @@ __global__ __launch_bounds__(kOpThreads<DIM>, DIM == 3 ? NW3 / 4 : (NV <= 32 ? 2
       u[c * N + g] = y[c];
       acc[0] += w[c] * y[c];
     }
-    if constexpr (!FIRST) {
+    if constexpr (NV > 0) {
 #pragma unroll
       for (int q0 = 0; q0 < NV; q0 += kQ) {
         if (q0 < j) {
@@ -712,7 +714,7 @@ __global__ __launch_bounds__(kOpThreads<DIM>, DIM == 3 ? NW3 / 4 : (NV <= 32 ? 2
   // partial sums: w~.u, s_0 .. s_{j-1}, z_0 .. z_{j-1}
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
 #pragma unroll
-  for (int q = 0; q <= (FIRST ? 0 : 2 * NV); ++q) {
+  for (int q = 0; q <= 2 * NV; ++q) {
     const int k = q <= NV ? q : q - NV;  // 1 + vector
     if (k <= j) {
       double v = acc[q];
@@ -722,7 +724,7 @@ __global__ __launch_bounds__(kOpThreads<DIM>, DIM == 3 ? NW3 / 4 : (NV <= 32 ? 2
     }
   }
   __syncthreads();
-  for (int q = threadIdx.x; q <= 2 * j; q += 64 * NW) {
+  for (int q = threadIdx.x; q <= (NV > 0 ? 2 * j : 0); q += 64 * NW) {
     double s = lds[q];
 #pragma unroll
     for (int w = 1; w < NW; ++w) s += lds[w * (2 * NV + 1) + q];
@@ -733,6 +735,64 @@ __global__ __launch_bounds__(kOpThreads<DIM>, DIM == 3 ? NW3 / 4 : (NV <= 32 ? 2
 struct alignas(16) D2 {
   double x, y;
 };
+
+// The sums s = V^T w~ and z = V^T u of a column too long for the registers that
+// the operator leaves (gm_apply): kDots vectors at a time, over the same blocks
+// as the operator's, so that the partial sums lie where its own would.
+constexpr int kDots = 16, kDotThreads = 512;
+__global__ __launch_bounds__(kDotThreads) void k_gm_dots(GmBuf gm, int j) {
+  constexpr int NW = kDotThreads / 64;
+  __shared__ double lds[NW][2 * kDots];
+  __shared__ bool off;
+  const GmState *const st = gm.st;
+  if (threadIdx.x == 0) off = arnoldi_off(st, j);
+  __syncthreads();
+  if (off) return;
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  const double inv = 1.0 / st->wn;
+  const size_t n2 = gm.ld >> 1, ld2 = gm.ld >> 1;
+  const D2 *const V = reinterpret_cast<const D2 *>(gm.V);
+  for (int q0 = 0; q0 < j; q0 += kDots) {
+    double acc[2 * kDots];
+#pragma unroll
+    for (int q = 0; q < 2 * kDots; ++q) acc[q] = 0.0;
+    for (size_t i = (size_t)blockIdx.x * kDotThreads + threadIdx.x; i < n2; i += (size_t)gridDim.x * kDotThreads) {
+      const D2 w = V[(size_t)j * ld2 + i], u = V[(size_t)(j + 1) * ld2 + i];
+#pragma unroll
+      for (int q1 = 0; q1 < kDots; q1 += 2 * kQ) {
+        if (q0 + q1 < j) {
+          D2 v[2 * kQ];
+#pragma unroll
+          for (int q = 0; q < 2 * kQ; ++q) v[q] = V[(size_t)min(q0 + q1 + q, j - 1) * ld2 + i];
+#pragma unroll
+          for (int q = 0; q < 2 * kQ; ++q) {
+            acc[q1 + q] += v[q].x * w.x + v[q].y * w.y;
+            acc[kDots + q1 + q] += v[q].x * u.x + v[q].y * u.y;
+          }
+        }
+      }
+    }
+#pragma unroll
+    for (int q = 0; q < 2 * kDots; ++q) {
+      if (q0 + q % kDots < j) {
+        double v = acc[q];
+#pragma unroll
+        for (int o = 32; o >= 1; o >>= 1) v += __shfl_xor(v, o);
+        if (lane == 0) lds[wid][q] = v;
+      }
+    }
+    __syncthreads();
+    const int q = threadIdx.x;
+    if (q < 2 * kDots && q0 + q % kDots < j) {
+      double s = lds[0][q];
+#pragma unroll
+      for (int w = 1; w < NW; ++w) s += lds[w][q];
+      const int at = 1 + q0 + (q < kDots ? q : j + q - kDots);
+      gm.p1[(size_t)at * gridDim.x + blockIdx.x] = q < kDots ? inv * s : s;
+    }
+    __syncthreads();
+  }
+}
 
 // Column j of the Hessenberg matrix and the rotations (one wave): s, z and
 // z_j as in k_gm_ortho, hh: room for 2 (kMaxRestart + 1) values in LDS.
@@ -1011,20 +1071,31 @@ __global__ __launch_bounds__(TB) void k_gm_adj_finish(KParams kp, GmBuf gm, cons
     }                                                            \
   } while (0)
 
+// The operator sums a column's dots along the way while the sums fit beside it in
+// the registers: 16 vectors in 2D (12 registers spilled with M in FP64, none in
+// FP32), 8 in 3D.  Past that k_gm_dots sums them all from a second read of w~ and
+// u.  Before that the operator had variants of 16 (3D), 32 and 64 vectors that
+// spilled up to 638 registers; ms for 14 and 25 steps of 30 and 60 of 64, then and
+// now: 256 x 128 x 128 26.2, 53.4, 214 and 25.3, 47.8, 151; 64 x 48 x 40 0.98,
+// 2.31, 12.7 and 0.94, 1.92, 7.0; 625 x 625 1.15, 2.91, 13.3 and 1.15, 2.71, 12.2.
 template <int DIM, bool TR, typename MT>
 void gm_apply(const KParams &kp, const GmBuf &gm, const void *Mv, int j, bool cycle0, int nb, hipStream_t st) {
   const MT *M = static_cast<const MT *>(Mv);
+#define RELSIM_GM_APPLY(NV, FIRST)                                                                                  \
+  hipLaunchKernelGGL((k_gm_apply<DIM, TR, MT, NV, FIRST>), dim3(nb), dim3(kOpThreads<DIM>), 0, st, kp, gm, M, j,    \
+                     cycle0 ? 1 : 0)
   if (j == 0)
-    hipLaunchKernelGGL((k_gm_apply<DIM, TR, MT, 1, true>), dim3(nb), dim3(kOpThreads<DIM>), 0, st, kp, gm, M, j,
-                       cycle0 ? 1 : 0);
+    RELSIM_GM_APPLY(0, true);
   else if (j <= 8)
-    hipLaunchKernelGGL((k_gm_apply<DIM, TR, MT, 8, false>), dim3(nb), dim3(kOpThreads<DIM>), 0, st, kp, gm, M, j, 0);
-  else if (j <= 16)
-    hipLaunchKernelGGL((k_gm_apply<DIM, TR, MT, 16, false>), dim3(nb), dim3(kOpThreads<DIM>), 0, st, kp, gm, M, j, 0);
-  else if (j <= 32)
-    hipLaunchKernelGGL((k_gm_apply<DIM, TR, MT, 32, false>), dim3(nb), dim3(kOpThreads<DIM>), 0, st, kp, gm, M, j, 0);
-  else
-    hipLaunchKernelGGL((k_gm_apply<DIM, TR, MT, 64, false>), dim3(nb), dim3(kOpThreads<DIM>), 0, st, kp, gm, M, j, 0);
+    RELSIM_GM_APPLY(8, false);
+  else if (DIM == 2 && j <= 16)
+    RELSIM_GM_APPLY(DIM == 2 ? 16 : 8, false);
+  else {
+    RELSIM_GM_APPLY(0, false);
+    // the call after the last column only finds the cycle's end
+    if (j < gm.m) hipLaunchKernelGGL(k_gm_dots, dim3(nb), dim3(kDotThreads), 0, st, gm, j);
+  }
+#undef RELSIM_GM_APPLY
 }
 
 void gm_residual(const KParams &kp, const GmBuf &gm, int mass_fp32, bool transpose, const void *M, const double *x,
