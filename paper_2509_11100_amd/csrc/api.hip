@@ -311,7 +311,6 @@ KParams make_kparams(const relsim_params *p) {
   k.f_inv_dx = (float)k.inv_dx;
   k.f_inv_dy = (float)k.inv_dy;
   k.f_inv_dz = (float)k.inv_dz;
-  if (p->dim == 3) plan_tiles3(k);
   return k;
 }
 
@@ -529,6 +528,7 @@ int relsim_init(const relsim_params *p, void *hip_stream, void *workspace, size_
   c->p = *p;
   if (c->p.dim == 2) c->p.nz = 1;
   c->kp = make_kparams(&c->p);
+  if (c->p.dim == 3) plan_tiles3(c->kp);  // not in make_kparams: calls without a context do no solve
   c->L = L;
   c->st = (hipStream_t)hip_stream;
   c->ws = (char *)workspace;
@@ -546,7 +546,6 @@ int relsim_init(const relsim_params *p, void *hip_stream, void *workspace, size_
     relsim_finalize(c);
     return RELSIM_EHIP;
   }
-  // processing order of the particle kernels: tile-major slot -> cell table
   if (hipGetLastError() != hipSuccess) {
     relsim_finalize(c);
     return RELSIM_EHIP;
