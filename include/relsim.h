@@ -257,7 +257,7 @@ int relsim_placement_clamps(relsim_ctx *ctx, int64_t *count);
 
 /* Write part->cell (front set) from bin_start: particle p of bin b gets cell
  * b / nspecies.  Needed after relsim_push before anything reads the cell
- * ids (the adjoint entry points read state_n->cell). */
+ * ids (relsim_sort; the caller's own code). */
 int relsim_fill_cells(relsim_ctx *ctx, relsim_particles *part);
 
 /* a7 (S7): out[0..3] = kinetic, electric, magnetic, total energy (host
@@ -316,9 +316,9 @@ int relsim_apply_AT(relsim_ctx *ctx, const void *M, const double *x, double *out
  * accumulators zeroed by the caller first.
  *
  * relsim_push_adjoint (adjoint of S1, S2, S6): state_n is the particle state
- * before the push (bin-sorted, with its cell ids written, e.g. by
- * relsim_fill_cells); new_index maps it to the
- * order of lam_x_in / lam_u_in (the cotangents of x^{n+3/2}, u^{n+1}; NULL =
+ * before the push, bin-sorted (the bins say where each particle is; its cell
+ * array must be given, a null pointer is refused, but is not read); new_index
+ * maps it to the order of lam_x_in / lam_u_in (the cotangents of x^{n+3/2}, u^{n+1}; NULL =
  * same order).  Writes lam_x_out, lam_u_out (cotangents of x^{n+1/2}, u^n
  * through the push) and ADDS into lam_E_theta and lam_B_n. */
 int relsim_push_adjoint(relsim_ctx *ctx, const relsim_particles *state_n, const double *E_theta, const double *B_n,

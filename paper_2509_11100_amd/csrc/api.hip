@@ -913,6 +913,9 @@ int relsim_apply_AT(relsim_ctx *c, const void *M, const double *x, double *out) 
   return launch_status(c, "relsim_apply_AT");
 }
 
+// The adjoints' particles.  The kernels take each cell's particles from the
+// bins; the entry points go on refusing a state without its cell array, as
+// callers may count on.
 static AdjInPtrs adj_inputs(const relsim_particles *pt) {
   AdjInPtrs a;
   a.bin_start = pt->bin_start;

@@ -1123,7 +1123,11 @@ void launch_apply(const KParams &kp, int mass_fp32, bool transpose, const void *
 // side is the neighbour's), and the ty <= kRows3 rows and lz planes for which
 // the tiles read least, each with 9 of the 14 blocks of a row and of a plane
 // of its neighbours, while the tiles, one to a CU at a time, keep 85 % of the
-// 256 CUs busy; fewer busy CUs count against them in proportion.
+// 256 CUs busy; fewer busy CUs count against them in proportion.  Solve, us, M in
+// FP64, with 70, 85 and 95 %: 64 x 48 x 40 639, 588 and 579, 96 x 47 x 33 628, 650
+// and 676, 128 x 64 x 64 2291, 2094 and 2106, 120 x 100 x 90 3980, 3773 and 3772,
+// 256 x 128 x 128 14820, 14880 and 13690.  The width of a row is not weighed: one
+// of 64 nodes takes two tiles of 32 in 34 of the 64 lanes, one of 16 nodes 18.
 void plan_tiles3(KParams &kp) {
   const int ntx = (kp.nx + 61) / 62;
   kp.t3x = (kp.nx + ntx - 1) / ntx;

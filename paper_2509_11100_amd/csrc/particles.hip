@@ -400,15 +400,6 @@ __device__ __forceinline__ T inv_gbar(const KParams &kp, const PC<T> &pc, const 
 // ---------------------------------------------------------------------------
 // S1-S3: per-cell moments
 // ---------------------------------------------------------------------------
-// 2D: the G lanes of a group split the cell's particles; each lane sums all
-// 93 moments (81 mass, 12 current) of its particles, and the group's G
-// partial sums are then added in fixed lane order.  In FP64 the 93 sums take
-// 186 of the 256 registers that two waves to a SIMD leave, too many beside two
-// records: with the next one in registers a SIMD held one wave, and the
-// compiler's cut to two waves spilled inside the loop (161 us, and 202, for
-// 10.4M particles, 512 per cell).  The next record is therefore loaded straight
-// into LDS and a round reads its own from there: 145 us, 3.4 TB/s.  32 rounds
-// of G stay the best size of a group (16: 151 us, 8: 172).
 // A 2D FP64 record travels from memory to LDS without passing through
 // registers: lane l's three 16-byte pieces (offsets, u_x u_y, u_z w) go to
 // 16 l in the three KiB at dst.
@@ -422,6 +413,18 @@ __device__ __forceinline__ void lds_load_rec(int q, const V2<double> *__restrict
   __builtin_amdgcn_global_load_lds((GP)(b + 16), (LP)(dst + 2048), 16, 0, 0);
 }
 
+// 2D: the G lanes of a group split the cell's particles; each lane sums all
+// 93 moments (81 mass, 12 current) of its particles, and the group's G
+// partial sums are then added in fixed lane order.  In FP64 the 93 sums take
+// 186 of the 256 registers that two waves to a SIMD leave, too many beside two
+// records: with the next one in registers a SIMD held one wave, and the
+// compiler's cut to two waves spilled inside the loop (161 us, and 202, for
+// 10.4M particles, 512 per cell).  The next record is therefore loaded straight
+// into LDS and a round reads its own from there: 145 us, 3.4 TB/s.  32 rounds
+// of G stay the best size of a group (16: 151 us, 8: 172).  A wave alone
+// on its SIMD takes longer for a round than with the record in registers (1.4 us
+// against 1.15): choose_group gives launches that would end in such waves 8
+// lanes per cell.
 template <typename T, int G, bool GB>
 __global__ __launch_bounds__(64, sizeof(T) == 8 ? 2 : 1) void k_deposit_cells(KParams kp, const int32_t *__restrict__ bin_start,
                                                       const V2<T> *__restrict__ xy,
@@ -1011,8 +1014,8 @@ __device__ __forceinline__ Segment<T, DIM> stage_segment(const KParams &kp, cons
                                                          unsigned char *smem, int lane) {
   Segment<T, DIM> sg;
   const int S = kp.nspecies;
-  // segments are visited tile by tile (tiles of about 16 x sty x stz cells,
-  // segments row-major inside a tile), as the other particle kernels visit
+  // segments are visited tile by tile (tiles of tl.spr segments x sty x stz
+  // cells, segments row-major inside a tile), as the other particle kernels visit
   // cells: the destinations of neighbouring sources are then written close
   // together in time
   int C = tl.C;

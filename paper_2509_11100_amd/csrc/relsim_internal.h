@@ -38,9 +38,18 @@ struct Layout {
 
 constexpr int kMaxRestart = 64;
 constexpr int kGmThreads = 256;     // threads per block of the GMRES kernels
-constexpr int kGmNodeBlocks = 512;  // most blocks of the 2D operator's GMRES kernels (a multiple of 8)
-constexpr int kGmTileBlocks = 1024; // most blocks of the 3D operator's (a multiple of 8)
-constexpr int kGmVecBlocks = 512;   // most blocks of the others
+// Most blocks of the 2D operator's GMRES kernels, of the 3D operator's (whose
+// plan seldom has more tiles) and of the others; the first two multiples of 8.
+// A block that takes several parts of the grid leaves fewer partial sums, which
+// every block of the next kernel adds up; too few leave CUs idle.  Solve, us,
+// evenly filled, M in FP64, with 256, 512, 1024 and 2048 blocks: 2D operator, 625
+// x 625 1059, 927, 1030 and 1159, 1024 x 512 1492, 1279, 1376 and 1567; others,
+// 625 x 625 953, 927, 934 and 952, 256 x 128 x 128 15070, 14880, 14870 and 14980.
+// The 3D operator with 256, 512, 1024 and 2048: 128 x 64 x 64 2091, 2085, 2094
+// and 2094, 256 x 128 x 128 14910, 14880, 14880 and 14860.
+constexpr int kGmNodeBlocks = 512;
+constexpr int kGmTileBlocks = 1024;
+constexpr int kGmVecBlocks = 512;
 constexpr int kRedBlocks = 1024;    // blocks of the energy reductions
 constexpr int kSinkSlots = 512;     // per-lane store sinks of the particle kernels (power of two), 32 B each
 
