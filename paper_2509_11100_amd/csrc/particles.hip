@@ -425,8 +425,8 @@ __device__ __forceinline__ void lds_load_rec(int q, const V2<double> *__restrict
 // on its SIMD takes longer for a round than with the record in registers (1.4 us
 // against 1.15): choose_group gives launches that would end in such waves 8
 // lanes per cell.
-template <typename T, int G, bool GB>
-__global__ __launch_bounds__(64, sizeof(T) == 8 ? 2 : 1) void k_deposit_cells(KParams kp, const int32_t *__restrict__ bin_start,
+template <typename T, int G, bool GB, bool VIA_LDS>
+__global__ __launch_bounds__(64, VIA_LDS ? 2 : 1) void k_deposit_cells(KParams kp, const int32_t *__restrict__ bin_start,
                                                       const V2<T> *__restrict__ xy,
                                                       const V4<T> *__restrict__ uw,
                                                       const V4<T> *__restrict__ Bs, T *__restrict__ S,
@@ -452,9 +452,9 @@ __global__ __launch_bounds__(64, sizeof(T) == 8 ? 2 : 1) void k_deposit_cells(KP
   for (int k = 0; k < NACC; ++k) acc[k] = T(0);
   PRec<T> cur{}, nxt{};
   int p = pal + gl;
-  // FP64: the accumulators leave no registers for a record in flight, so it
-  // waits in LDS, in one of two buffers that share the reduction's room
-  constexpr bool VIA_LDS = sizeof(T) == 8;
+  // VIA_LDS (FP64): the record in flight waits in one of two buffers that share
+  // the reduction's room
+  static_assert(!VIA_LDS || sizeof(T) == 8);
   char *const recs = reinterpret_cast<char *>(red);
   if (rounds > 0) {
     if constexpr (VIA_LDS)
@@ -1689,15 +1689,25 @@ T *mp(void *p) {
   return static_cast<T *>(p);
 }
 
+template <typename T, int G, bool VIA_LDS>
+void deposit_launch(const KParams &kp, const PartPtrs &pp, const void *Bst, void *S, int nblk, hipStream_t st) {
+  if (pp.gbar)
+    hipLaunchKernelGGL((k_deposit_cells<T, G, true, VIA_LDS>), dim3(nblk), dim3(64), 0, st, kp, pp.bin_start,
+                       cp<V2<T>>(pp.xy), cp<V4<T>>(pp.uw), cp<V4<T>>(Bst), mp<T>(S), cp<T>(pp.gbar));
+  else
+    hipLaunchKernelGGL((k_deposit_cells<T, G, false, VIA_LDS>), dim3(nblk), dim3(64), 0, st, kp, pp.bin_start,
+                       cp<V2<T>>(pp.xy), cp<V4<T>>(pp.uw), cp<V4<T>>(Bst), mp<T>(S), nullptr);
+}
+
+// FP64 records wait in LDS where two waves can share a SIMD.  Up to 1024 waves
+// each has a SIMD to itself, and the record waits in registers: 61 x 63 cells,
+// 256 per cell, 28.1 -> 27.3 us with the assembly, 100 x 77 41.2 -> 40.1.
 template <typename T, int G>
 void deposit_impl(const KParams &kp, const PartPtrs &pp, const void *Bst, void *S, hipStream_t st) {
   const int nblk = (kp.ncells + (64 / G) - 1) / (64 / G);
-  if (pp.gbar)
-    hipLaunchKernelGGL((k_deposit_cells<T, G, true>), dim3(nblk), dim3(64), 0, st, kp, pp.bin_start,
-                       cp<V2<T>>(pp.xy), cp<V4<T>>(pp.uw), cp<V4<T>>(Bst), mp<T>(S), cp<T>(pp.gbar));
-  else
-    hipLaunchKernelGGL((k_deposit_cells<T, G, false>), dim3(nblk), dim3(64), 0, st, kp, pp.bin_start,
-                       cp<V2<T>>(pp.xy), cp<V4<T>>(pp.uw), cp<V4<T>>(Bst), mp<T>(S), nullptr);
+  if constexpr (sizeof(T) == 8)
+    if (nblk > 1024) return deposit_launch<T, G, true>(kp, pp, Bst, S, nblk, st);
+  deposit_launch<T, G, false>(kp, pp, Bst, S, nblk, st);
 }
 
 template <typename T>
