@@ -295,9 +295,11 @@ __device__ __forceinline__ void species(const KParams &kp, const int32_t *__rest
     }
 }
 
-// Both kernels move about 130 bytes per particle and take 101 and 80 us for
-// the 2.1M particles of the 256 x 128 sheet (2.7 and 3.3 TB/s; 59 and 57 us at
-// the copy rate; with the lanes summed by wave butterflies per particle and
+// Both kernels need about 130 bytes per particle and take 95 to 101 and 75 to 80
+// us for the 2.1M particles of the 256 x 128 sheet.  Counted, with the cells' sums,
+// they move 0.42 and 0.32 GB, 4.4 and 4.3 TB/s, with the VALU busy 0.30 and 0.35
+// of the time: they run at the memory's rate (59 and 57 us for the bytes needed
+// at the copy rate; with the lanes summed by wave butterflies per particle and
 // added by atomics they took 445 and 305 us).  In 2D they hold 39 and 27 sums
 // per lane and fit two waves per SIMD without spilling; forcing three spills
 // (1865 us for the step instead of 1350), and so does loading the next

@@ -224,7 +224,8 @@ __device__ __forceinline__ void apply_node(const KParams &kp, const MT *__restri
 // by the tile: a lane on either side of the row, a wave before (6 of 14
 // blocks) and a wave behind (3) and the plane before the first (9).  The curl
 // of the curl comes along: t = C_NC x of the wave's cells, shifted and passed
-// the same way.  Counted 5.5 GB, 1.18 ms (4.7 TB/s); tiles of 2, 6, 8, 10 and
+// the same way.  Counted for k_gm_residual, which also reads b and writes r: 6.1
+// GB, 1.25 ms (4.9 TB/s); the product alone 1.18 ms; tiles of 2, 6, 8, 10 and
 // 14 rows took 14.9, 14.2, 14.3, 14.3 and 15.2 ms for the whole solve (the
 // last ones spill), and loading the next plane's first blocks ahead of the
 // exchange 14.2.  The blocks are loaded a row (of three) ahead of their use:
