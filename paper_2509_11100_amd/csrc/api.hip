@@ -336,7 +336,7 @@ PushPlan plan_push(const relsim_ctx *c, int64_t n, KernelKind k) {
   const size_t lds = 8192;
   const int nx = c->kp.nx;
   const double mean = (double)n / (double)c->kp.ncells;
-  auto reach = [&](int C) { return (nx + C - 1) / C * C; };
+  auto reach = [&](int C) { return (int64_t)((nx + C - 1) / C) * C; };
   int C = 1;
   while (C < 64 && 2.0 * C * mean <= rounds * 64.0 && 2 * C <= nx && c->kp.ncells / (2 * C) >= 2048 &&
          4 * reach(2 * C) <= 5 * reach(C) && push_lds_bytes(c->kp, c->p.precision, 2 * C) <= lds)
